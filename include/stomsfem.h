@@ -828,7 +828,7 @@ int stomsfem_plan_free(stomsfem_plan* plan);
  * Autotuner of the plain upscaling kernels.  For the batch's (m, a_dtype) on
  * the current device it times, with HIP events over `reps` launches after a
  * warm-up, every launch shape (workgroup size 64/128/256 of the per-lane
- * kernel for m <= 8; 1 or 2 wavefronts per workgroup of the tiled kernel for
+ * kernel for m <= 8; 1 or 2 wavefronts per workgroup of the row-distributed kernel for
  * m = 16, 32), keeps only shapes whose S equals the default shape's bit for
  * bit, then times FP64 against STOMSFEM_PREC_F32_REFINE64 on a prefix of
  * about 16384 pairs (the refined variant must agree to 1e-10 relative).  The

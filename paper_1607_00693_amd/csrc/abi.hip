@@ -24,8 +24,8 @@ namespace stomsfem {
 hipError_t launch_upscale_small(const UpArgs& args, int a_dtype, hipStream_t st, int block);
 hipError_t launch_upscale_ref(const UpArgs& args, int a_dtype, hipStream_t st);
 size_t upscale_ref_lds_bytes(int m);
-hipError_t launch_upscale_tiled(const UpArgs& args, int a_dtype, hipStream_t st, int waves);
-bool tiled_supports(int m);
+hipError_t launch_upscale_rows(const UpArgs& args, int a_dtype, hipStream_t st, int waves);
+bool rows_supports(int m);
 hipError_t launch_upscale_queue(const UpArgs* batches, int nb, int a_dtype, unsigned long long* counter,
                                 hipStream_t st);
 bool queue_supports(int m);
@@ -248,7 +248,7 @@ std::atomic<uint64_t> g_refine_pairs{0}, g_refine_recomputed{0}, g_interp_pairs{
 // coefficient dtype), chosen by stomsfem_autotune (defaults otherwise).
 struct LaunchCfg {
   int lane_block = 64;   // workgroup size of the per-lane kernel (m <= 8)
-  int tiled_waves = 1;   // wavefronts per workgroup of the tiled kernel (m = 16, 32)
+  int tiled_waves = 1;   // wavefronts per workgroup of the row-distributed kernel (m = 16, 32)
   int precision = STOMSFEM_PREC_F64;
   double ms_default = 0.0, ms_best = 0.0;
   int tuned = 0;
@@ -266,7 +266,7 @@ LaunchCfg tuned_cfg(int m, int a_dtype) {
 
 hipError_t launch_upscale_cfg(const UpArgs& args, int a_dtype, hipStream_t st, const LaunchCfg& c) {
   if (args.m <= 8) return launch_upscale_small(args, a_dtype, st, c.lane_block);
-  if (tiled_supports(args.m)) return launch_upscale_tiled(args, a_dtype, st, c.tiled_waves);
+  if (rows_supports(args.m)) return launch_upscale_rows(args, a_dtype, st, c.tiled_waves);
   return launch_upscale_ref(args, a_dtype, st);
 }
 
@@ -2777,7 +2777,7 @@ int stomsfem_autotune(const stomsfem_batch* batch, int32_t reps, stomsfem_tuning
   std::vector<LaunchCfg> shapes;
   if (b.m <= 8) {
     for (int bs : {64, 128, 256}) shapes.push_back(LaunchCfg{bs, 1});
-  } else if (tiled_supports(b.m)) {
+  } else if (b.m == 16 || b.m == 32) {
     for (int wv : {1, 2}) shapes.push_back(LaunchCfg{64, wv});
   } else {
     shapes.push_back(LaunchCfg{});

@@ -1,0 +1,47 @@
+"""The row-distributed cell solver (9 <= m <= 32) at the edges of its layout:
+bandwidths around its 16-row blocks, m with and without a kernel of its own,
+pair counts that are not a multiple of a wavefront's four.
+
+Tolerance: both sides factor SPD systems in FP64; on log-normal media
+exp(1.5 N(0,1)) (four decades between neighbouring elements) the condition
+numbers stay below about 1e5, so 1e-10 relative to max|S| per pair leaves
+room for the different elimination orders, as on the other plain kernels."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1607_00693_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+STOL = 1e-10
+
+
+@pytest.mark.parametrize("m", [9, 10, 15, 16, 17, 18, 24, 31, 32])
+@pytest.mark.parametrize("ncx,ncy,N", [(1, 1, 1), (3, 2, 3)])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_rows_kernel_matches_oracle(orc, m, ncx, ncy, N, dtype):
+    from paper_1607_00693_amd import stomsfem as sm
+
+    print(f"[rows] m={m} ncx={ncx} ncy={ncy} N={N} {dtype.__name__}", flush=True)
+    a = W.lognormal_field((N, ncy * m, ncx * m), 1.5, 300 + m).astype(dtype)
+    status = torch.full((N, ncx * ncy), 7, dtype=torch.int32, device="cuda")
+    S = sm.upscale(torch.from_numpy(a).cuda(), ncx, ncy, m, status=status).cpu().numpy()
+    S_ref, _, _ = orc.upscale(a.astype(np.float64), ncx, ncy, m)
+    assert (status.cpu().numpy() == 0).all()
+    assert (np.abs(S - S_ref).max(-1) / np.abs(S_ref).max(-1)).max() < STOL
+
+
+@pytest.mark.parametrize("m", [12, 16, 32])
+def test_rows_kernel_flags_only_the_bad_pair(m):
+    from paper_1607_00693_amd import stomsfem as sm
+
+    # five pairs in a row of elements: the bad ones share wavefronts with good ones
+    a = W.lognormal_field((1, m, 5 * m), 0.5, 910 + m)
+    good = sm.upscale(torch.from_numpy(a).cuda(), 5, 1, m).cpu().numpy()
+    a[0, m // 2, m + 2] = -50.0
+    a[0, 3, 3 * m + 1] = np.nan
+    status = torch.zeros((1, 5), dtype=torch.int32, device="cuda")
+    S = sm.upscale(torch.from_numpy(a).cuda(), 5, 1, m, status=status).cpu().numpy()
+    assert list(status.cpu().numpy()[0] != 0) == [False, True, False, True, False]
+    assert (S[0, [0, 2, 4]] == good[0, [0, 2, 4]]).all()
