@@ -127,6 +127,26 @@ __device__ __forceinline__ void row_rhs3_own(double* f, double nl) {
       : "v"(nl), "n"(L));
 }
 
+// g[v] += z[v](lane L of the row) * c for ten right-hand sides
+template <int L>
+__device__ __forceinline__ void row_rhs10(double* g, const double* z, double c) {
+  asm("s_nop 1\n\t" BR_DPP("%0", "%10", "%20", "%21") BR_DPP("%1", "%11", "%20", "%21")
+          BR_DPP("%2", "%12", "%20", "%21") BR_DPP("%3", "%13", "%20", "%21") BR_DPP("%4", "%14", "%20", "%21")
+              BR_DPP("%5", "%15", "%20", "%21") BR_DPP("%6", "%16", "%20", "%21") BR_DPP("%7", "%17", "%20", "%21")
+                  BR_DPP("%8", "%18", "%20", "%21") BR_DPP("%9", "%19", "%20", "%21")
+      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7]), "+v"(g[8]),
+        "+v"(g[9])
+      : "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "v"(z[4]), "v"(z[5]), "v"(z[6]), "v"(z[7]), "v"(z[8]), "v"(z[9]),
+        "v"(c), "n"(L));
+}
+
+// acc[i] += y(lane i of the row) * nl, i < 3
+__device__ __forceinline__ void row_lifts3(double* acc, double y, double nl) {
+  asm("s_nop 1\n\t" BR_DPP("%0", "%3", "%4", "0") BR_DPP("%1", "%3", "%4", "1") BR_DPP("%2", "%3", "%4", "2")
+      : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2])
+      : "v"(y), "v"(nl));
+}
+
 // Lane masks of the four rows of a wavefront as a scalar constant.
 __host__ __device__ constexpr unsigned long long row_mask_at(int r) { return 0x0001000100010001ull << r; }
 __host__ __device__ constexpr unsigned long long row_mask_above(int r) {
@@ -176,6 +196,91 @@ struct RowWindow {
       for (int i = 0; i < NS; ++i) diag[i][c] = sub[i][c] = 0.0;
       far[c] = 0.0;
     }
+  }
+};
+
+// LDS image that spreads the 16 entering rows' couplings over the columns of
+// one problem: row 16 (P + NS) + r of a (n = M - 1)-wide nine-point grid has
+// SW, S, SE at offsets -M, -M + 1, -M + 2 and W, D at -1, 0.  The columns left
+// of block NS and those of block NS take turns in 18 cells per row (column
+// OFF + i at cell i + 1, OFF = 16 NS - M; then column 16 NS + c at cell
+// c + 1), every unused cell stays zero, cells 0 and 19 always are, and cell 20
+// takes what lies outside.  W of row 0 belongs to the block before and is
+// added in registers.  M >= 4.
+template <int NS, int MC>
+struct RowImage {
+  static constexpr int LD = 21, SIZE = 16 * LD;  // doubles per problem
+  double* row;
+  int r, M;
+  __device__ __forceinline__ void init(double* img, int r_, int M_) {
+    r = r_;
+    M = M_;
+    row = img + r * LD;
+    for (int c = 0; c < LD; ++c) row[c] = 0.0;
+  }
+  // couplings (of this lane's row) inside block NS: cell, or the dump cell
+  __device__ __forceinline__ int inner(int t) const { return r + t >= M ? r + t - M + 1 : 20; }
+  __device__ __forceinline__ void put_left(double eSW, double eS, double eSE) {
+    row[r] = 0.0;
+    if (MC == 0 || MC < 18)
+      for (int t = 0; t < 3; ++t) row[inner(t)] = 0.0;
+    row[r + 1] = eSW;
+    row[r + 2] = eS;
+    row[r + 3] = eSE;
+  }
+  __device__ __forceinline__ void put_diag(double eSW, double eS, double eSE, double eW, double eD) {
+    row[r + 2] = row[r + 3] = 0.0;
+    row[r + 1] = eD;
+    row[r == 0 ? 20 : r] = eW;
+    if (MC == 0 || MC < 18) {
+      row[inner(0)] = eSW;
+      row[inner(1)] = eS;
+      row[inner(2)] = eSE;
+    }
+  }
+  // column q < 16 NS (after put_left), eW = this row's W coupling
+  __device__ __forceinline__ double left(int q, double eW) const {
+    const int i = q - (16 * NS - (MC ? MC : M));
+    double v = 0.0;
+    if (MC == 0)
+      v = row[(i < -1 ? -1 : i > 18 ? 18 : i) + 1];
+    else if (i >= 0 && i < 18)
+      v = row[i + 1];
+    if (q == 16 * NS - 1) v += __builtin_amdgcn_inverse_ballot_w64(row_mask_at(0)) ? eW : 0.0;
+    return v;
+  }
+  // column c of block NS (after put_diag)
+  __device__ __forceinline__ double diag(int c) const { return row[c + 1]; }
+};
+
+// f += bilinear data: (K p^l) at a node from its four element coefficients,
+// l = 0, 1, 2, on a grid of 1/rm cells per side whose element south-west of
+// the node has its centre at (xw, ys).  Linear in the coefficients, so
+// elements that do not count are passed as 0.
+__device__ __forceinline__ void bilinear_load(double aSW, double aSE, double aNW, double aNE, double xw, double ys,
+                                              double rm, double* f) {
+  const double h2 = 0.5 * rm, t6 = rm * rm * (1.0 / 6.0);
+  const double dS = aSW - aSE, dN = aNW - aNE, dW = aSW - aNW, dE = aSE - aNE;
+  const double P0 = dS + dN, Q0 = dW + dE;
+  const double P1 = ys * P0 + rm * dN, Q1 = xw * Q0 + rm * dE;
+  const double T = t6 * (dS - dN);
+  f[0] = h2 * ((P1 - P0) + (Q1 - Q0)) + T;
+  f[1] = h2 * ((P0 - P1) - Q1) - T;
+  f[2] = h2 * (P1 + Q1) + T;
+}
+
+// Nine-point couplings of an interior node to its lower neighbours, and its
+// diagonal, from the four element coefficients; rows past the grid are
+// identity rows.
+struct NodeRow {
+  double SW, S, SE, W, D;
+  __device__ __forceinline__ void set(const double* q4, int ix, int iy, int n) {
+    const bool in = iy < n, w = ix >= 1, so = iy >= 1;
+    SW = (in && w && so) ? -q4[0] * (1.0 / 3.0) : 0.0;
+    S = (in && so) ? -(q4[0] + q4[1]) * (1.0 / 6.0) : 0.0;
+    SE = (in && so && ix <= n - 2) ? -q4[1] * (1.0 / 3.0) : 0.0;
+    W = (in && w) ? -(q4[0] + q4[2]) * (1.0 / 6.0) : 0.0;
+    D = in ? (2.0 / 3.0) * ((q4[0] + q4[1]) + (q4[2] + q4[3])) : 1.0;
   }
 };
 

@@ -18,6 +18,15 @@ struct UpArgs {
   int32_t bc;         // boundary data of the cell problems: 0 linear, 1 oscillatory (reference kernel only)
 };
 
+// Workgroups of a launch as a grid whose x extent stays within the limit of
+// 2^32 threads per dimension, and a workgroup's number in it (the last row
+// may hold workgroups past the end).
+inline dim3 grid_of_blocks(int64_t blocks) {
+  constexpr int64_t X = 1 << 24;
+  return blocks <= X ? dim3((unsigned)blocks) : dim3((unsigned)X, (unsigned)((blocks + X - 1) / X));
+}
+__device__ __forceinline__ int64_t linear_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Row-major offset of the m x m block of coarse element K of sample s.
 __device__ __forceinline__ int64_t block_offset(int64_t s, int K, int ncx, int ncy, int m) {
   const int64_t lda = (int64_t)ncx * m;

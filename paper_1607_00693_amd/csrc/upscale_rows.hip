@@ -33,37 +33,14 @@ namespace stomsfem {
 
 constexpr int RW_PAIRS = 4;  // pairs per wavefront
 
-// LDS image of the 16 entering rows of one pair: the columns of row
-// 16 (P + NS) + r relative to column 16 P of the panel.  Nonzeros sit at
-// q0 + r .. q0 + r + 2 (SW, S, SE; q0 = 16 NS - m) and 16 NS + r - 1, + r (W,
-// diagonal); every other entry stays zero from the start.
-//   m = 32: the columns 18 .. 30, always zero, are left out, so that the
-//     eight wavefronts that the registers allow fit a CU's LDS;
-//   m = 16: the columns 0 .. 17 and 15 .. 31 take turns in one image of 19
-//     columns (column q at q + 1, then column 16 + c at c + 1), so that twelve
-//     wavefronts fit instead of nine.
-template <int NS, int MC>
-struct RowImage {
-  static constexpr bool COMPACT = NS == 2 && MC == 32;
-  static constexpr bool TURNS = NS == 1 && MC == 16;
-  static constexpr int LD = COMPACT ? 36 : TURNS ? 19 : 16 * (NS + 1) + 1;
-  static constexpr int SIZE = 16 * LD;  // doubles per pair
-  static __device__ __forceinline__ constexpr bool has(int q) { return !COMPACT || q < 18 || q > 30; }
-  static __device__ __forceinline__ constexpr int at(int q) {
-    return COMPACT && q > 18 ? q - 12 : TURNS ? (q < 16 ? q + 1 : q - 15) : q;
-  }
-};
-
 // One wavefront's four pairs wtile * 4 + q.  MC: m at compile time, or 0
 // (m from the arguments, any 16 (NS - 1) < m <= 16 NS).  img: the wavefront's
 // LDS images.
 template <int NS, int MC, typename TA>
 __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int lane, double* img) {
-  using Img = RowImage<NS, MC>;
   const int M = MC ? MC : args.m;
   const int n = M - 1, NI = n * n, NP = (NI + 15) / 16;
   const int r = lane & 15;
-  double* row = img + (lane >> 4) * Img::SIZE + r * Img::LD;
 
   int64_t p = wtile * RW_PAIRS + (lane >> 4);
   const bool valid = p < args.npairs;
@@ -73,9 +50,9 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
   const int K = (int)(p - s * Mc);
   const TA* a = (const TA*)args.a + block_offset(s, K, args.ncx, args.ncy, M);
   const int64_t lda = (int64_t)args.ncx * M;
-  const double rm = 1.0 / M, h2 = 0.5 * rm, t6 = rm * rm / 6.0;
-
-  for (int c = 0; c < Img::LD; ++c) row[c] = 0.0;
+  const double rm = 1.0 / M;
+  RowImage<NS, MC> im;
+  im.init(img + (lane >> 4) * RowImage<NS, MC>::SIZE, r, M);
 
   // node of the row entering next, (ix, iy), and its four coefficients
   int ix = r % n, iy = r / n;
@@ -99,45 +76,23 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
 #pragma unroll
   for (int b = 0; b <= NS; ++b) f[b][0] = f[b][1] = f[b][2] = 0.0;
   double sc[6] = {0, 0, 0, 0, 0, 0};
-  bool bad = false;
-  double eS, eSE, eW, eD;
+  unsigned long long bad = 0;  // lanes whose pair met a pivot that is not positive
+  NodeRow e;
 
-  // row 16 (P + NS) + r: nonzeros to the LDS image, right-hand sides to
-  // f[NS], and the next row's coefficients on their way
+  // row 16 (P + NS) + r: couplings to the image, right-hand sides to f[NS];
+  // then the image's second turn, and the next row's coefficients on their way
   auto stage_row = [&]() {
-    const bool in = iy < n;
-    const double aSW = q4[0], aSE = q4[1], aNW = q4[2], aNE = q4[3];
-    const bool w = ix >= 1, so = iy >= 1;
-    const double eSW = (in && w && so) ? -aSW * (1.0 / 3.0) : 0.0;
-    eS = (in && so) ? -(aSW + aSE) * (1.0 / 6.0) : 0.0;
-    eSE = (in && so && ix <= n - 2) ? -aSE * (1.0 / 3.0) : 0.0;
-    eW = (in && w) ? -(aSW + aNW) * (1.0 / 6.0) : 0.0;
-    eD = in ? (2.0 / 3.0) * ((aSW + aSE) + (aNW + aNE)) : 1.0;
-    if constexpr (Img::TURNS) {
-      row[r] = 0.0;
-      if (r >= 14) row[1] = row[2] = 0.0;
-      row[r + 1] = eSW;
-      row[r + 2] = eS;
-      row[r + 3] = eSE;
-      if (r == 0) row[16] = eW;
-    } else {
-      const int q0 = 16 * NS - M + r;
-      row[Img::at(q0)] = eSW;
-      row[Img::at(q0 + 1)] = eS;
-      row[Img::at(q0 + 2)] = eSE;
-      row[Img::at(16 * NS + r - 1)] = eW;
-      row[Img::at(16 * NS + r)] = eD;
-    }
-    // (K p^l) at the node: gradients of p^l at the element centres (x south
-    // and north of the node, y west and east) and the twist term
-    const double dS = aSW - aSE, dN = aNW - aNE, dW = aSW - aNW, dE = aSE - aNE;
-    const double xw = (ix + 0.5) * rm, ys = (iy + 0.5) * rm;
-    const double P0 = dS + dN, Q0 = dW + dE;
-    const double P1 = ys * P0 + rm * dN, Q1 = xw * Q0 + rm * dE;
-    const double T = t6 * (dS - dN);
-    f[NS][0] = -(h2 * ((P1 - P0) + (Q1 - Q0)) + T);
-    f[NS][1] = -(h2 * ((P0 - P1) - Q1) - T);
-    f[NS][2] = -(h2 * (P1 + Q1) + T);
+    e.set(q4, ix, iy, n);
+    im.put_left(e.SW, e.S, e.SE);
+    bilinear_load(q4[0], q4[1], q4[2], q4[3], (ix + 0.5) * rm, (iy + 0.5) * rm, rm, f[NS]);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) f[NS][l] = -f[NS][l];
+    WAVE_SYNC();
+  };
+  auto stage_diag = [&]() {
+    WAVE_SYNC();
+    im.put_diag(e.SW, e.S, e.SE, e.W, e.D);
+    WAVE_SYNC();
     ix += 16;
     while (ix >= n) {
       ix -= n;
@@ -145,22 +100,6 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
     }
     load_quad();
   };
-  // the image's turn of the diagonal block (the other columns have been read)
-  auto stage_diag = [&]() {
-    if constexpr (Img::TURNS) {
-      WAVE_SYNC();
-      row[r + 2] = row[r + 3] = 0.0;
-      row[r] = eW;
-      row[r + 1] = eD;
-      if (r == 0) row[16] = 0.0;
-      if (r >= 14) row[1] = r == 14 ? eSE : eS;
-      if (r == 15) row[2] = eSE;
-      WAVE_SYNC();
-    }
-  };
-  // entering column q of the panel's window
-  auto entering = [&](int q) { return Img::has(q) ? row[Img::at(q)] : 0.0; };
-
   auto next_rhs = [&]() {
 #pragma unroll
     for (int i = 0; i < NS; ++i)
@@ -172,12 +111,13 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
   static_for<0, NS>([&](auto bc) {
     constexpr int b = decltype(bc)::value;
     stage_row();
-    if (b == 0) stage_diag();
-    WAVE_SYNC();
 #pragma unroll
-    for (int k = NS - b; k <= NS; ++k)
+    for (int k = NS - b; k < NS; ++k)
 #pragma unroll
-      for (int c = 0; c < 16; ++c) W.template block<b>(NS, k)[c] = entering(16 * k + c);
+      for (int c = 0; c < 16; ++c) W.template block<b>(NS, k)[c] = im.left(16 * k + c, e.W);
+    stage_diag();
+#pragma unroll
+    for (int c = 0; c < 16; ++c) W.template block<b>(NS, NS)[c] = im.diag(c);
     WAVE_SYNC();
     next_rhs();
   });
@@ -185,17 +125,17 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
   auto panel = [&](auto phase) {
     constexpr int PH = decltype(phase)::value;
     stage_row();
-    WAVE_SYNC();
 #pragma unroll
     for (int k = 0; k < NS; ++k)
 #pragma unroll
-      for (int c = 0; c < 16; ++c) W.template block<PH>(NS, k)[c] = entering(16 * k + c);
+      for (int c = 0; c < 16; ++c) W.template block<PH>(NS, k)[c] = im.left(16 * k + c, e.W);
     stage_diag();
     double own = 0.0;  // -1/d of the pivot row this lane holds
     double d = row_bcast<0>(W.template block<PH>(0, 0)[0]);
     static_for<0, 16>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      bad = bad || !(d > 0.0);
+      bad |= __builtin_amdgcn_ballot_w64(!(d > 0.0));
+      asm volatile("" : "+s"(bad));  // test the pivot here: it need not stay live
       const double ninv = neg_recip(d);
       own = __builtin_amdgcn_inverse_ballot_w64(row_mask_at(j)) ? ninv : own;
       // a pivot's own row and the rows above it keep their right-hand sides
@@ -208,7 +148,7 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
       }
       row_updates<j + 1, 16>(W.template block<PH>(0, 0), col[0], nl[0]);
       if constexpr (j < 15) d = row_bcast<j + 1>(W.template block<PH>(0, 0)[j + 1]);
-      W.template block<PH>(NS, NS)[j] = entering(16 * NS + j);
+      W.template block<PH>(NS, NS)[j] = im.diag(j);
       static_for<1, NS + 1>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
         row_updates<j + 1, 16>(W.template block<PH>(b, 0), col[0], nl[b]);
@@ -276,7 +216,7 @@ __device__ __forceinline__ void rows_wave(const UpArgs& args, int64_t wtile, int
   if (r == 0 && valid) {
     const double s3[3][3] = {{sc[0], sc[1], sc[2]}, {sc[1], sc[3], sc[4]}, {sc[2], sc[4], sc[5]}};
     store_packed(args.S + p * 10, s3);
-    if (args.status) args.status[p] = bad ? STOMSFEM_ENOTSPD : STOMSFEM_OK;
+    if (args.status) args.status[p] = ((bad >> lane) & 1) ? STOMSFEM_ENOTSPD : STOMSFEM_OK;
   }
 }
 
@@ -288,7 +228,7 @@ __global__ __launch_bounds__(64 * WV, (NS == 1 ? (MC == 16 ? 4 : 3) : 2)) void u
   // WV independent wavefronts per workgroup (a launch-shape choice only)
   __shared__ __attribute__((aligned(16))) double img[WV][RW_PAIRS * RowImage<NS, MC>::SIZE];
   const int wave = threadIdx.x >> 6;
-  rows_wave<NS, MC, TA>(args, (int64_t)blockIdx.x * WV + wave, threadIdx.x & 63, img[wave]);
+  rows_wave<NS, MC, TA>(args, linear_block() * WV + wave, threadIdx.x & 63, img[wave]);
 }
 bool rows_supports(int m) { return m >= 9 && m <= 32; }
 
@@ -297,9 +237,9 @@ static hipError_t launch_r(const UpArgs& args, int a_dtype, hipStream_t st) {
   const int64_t per_block = (int64_t)RW_PAIRS * WV;
   const int64_t blocks = (args.npairs + per_block - 1) / per_block;
   if (a_dtype == STOMSFEM_F32)
-    hipLaunchKernelGGL((upscale_rows_kernel<NS, MC, float, WV>), dim3((unsigned)blocks), dim3(64 * WV), 0, st, args);
+    hipLaunchKernelGGL((upscale_rows_kernel<NS, MC, float, WV>), grid_of_blocks(blocks), dim3(64 * WV), 0, st, args);
   else
-    hipLaunchKernelGGL((upscale_rows_kernel<NS, MC, double, WV>), dim3((unsigned)blocks), dim3(64 * WV), 0, st, args);
+    hipLaunchKernelGGL((upscale_rows_kernel<NS, MC, double, WV>), grid_of_blocks(blocks), dim3(64 * WV), 0, st, args);
   return hipGetLastError();
 }
 
@@ -351,10 +291,8 @@ __global__ void queue_reset_kernel(unsigned long long* counter) {
 
 template <typename TA>
 __global__ __launch_bounds__(128, 2) void upscale_queue_kernel(QueueArgs qa) {
-  // as large as either m needs, so that each wavefront's image stays its own
-  // whichever m its current item has
-  constexpr int S32 = RowImage<2, 32>::SIZE, S16 = RowImage<1, 16>::SIZE;
-  __shared__ __attribute__((aligned(16))) double lds[2][RW_PAIRS * (S32 > S16 ? S32 : S16)];
+  // the image has one size for every m
+  __shared__ __attribute__((aligned(16))) double lds[2][RW_PAIRS * RowImage<2, 32>::SIZE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (;;) {
     unsigned long long it = 0;

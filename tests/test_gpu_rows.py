@@ -45,3 +45,23 @@ def test_rows_kernel_flags_only_the_bad_pair(m):
     S = sm.upscale(torch.from_numpy(a).cuda(), 5, 1, m, status=status).cpu().numpy()
     assert list(status.cpu().numpy()[0] != 0) == [False, True, False, True, False]
     assert (S[0, [0, 2, 4]] == good[0, [0, 2, 4]]).all()
+
+
+@pytest.mark.parametrize("m,o", [(2, 0), (1, 1), (2, 1), (3, 1), (4, 2), (5, 2), (5, 5), (8, 4), (16, 0), (9, 4), (8, 8),
+                                 (11, 10), (16, 8), (11, 11), (40, 0), (20, 10), (17, 15), (16, 16), (17, 16), (28, 14),
+                                 (20, 20), (21, 21), (22, 21)])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_oversampled_kernels_match_oracle(orc, m, o, dtype):
+    # patches of 2 and 3 (one pair per lane), 4 ... 32 (four per wavefront; 4,
+    # 5, 9, 15 | 16, 17 | 31, 32 around the 16-row blocks) and 33 ... 64 (one per
+    # wavefront; 47, 48 | 49 between three and four row blocks); nine elements,
+    # two samples: 18 pairs, not a multiple of four
+    from paper_1607_00693_amd import stomsfem as sm
+
+    print(f"[rows] oversampled m={m} o={o} {dtype.__name__}", flush=True)
+    a = W.lognormal_field((2, 3 * m, 3 * m), 1.0, 400 + m + o).astype(dtype)
+    status = torch.full((2, 9), 7, dtype=torch.int32, device="cuda")
+    S = sm.upscale_os(torch.from_numpy(a).cuda(), 3, 3, m, o, status=status).cpu().numpy()
+    S_ref = orc.upscale_os(a.astype(np.float64), 3, 3, m, o)[0].reshape(S.shape)
+    assert (status.cpu().numpy() == 0).all()
+    assert (np.abs(S - S_ref).max(-1) / np.abs(S_ref).max(-1)).max() < STOL
