@@ -127,6 +127,16 @@ __device__ __forceinline__ void row_rhs3_own(double* f, double nl) {
       : "v"(nl), "n"(L));
 }
 
+// g += f(lane L of the row) * nl, and the same with f in the place of g
+template <int L>
+__device__ __forceinline__ void row_rhs1(double& g, double f, double nl) {
+  asm("s_nop 1\n\t" BR_DPP("%0", "%1", "%2", "%3") : "+v"(g) : "v"(f), "v"(nl), "n"(L));
+}
+template <int L>
+__device__ __forceinline__ void row_rhs1_own(double& f, double nl) {
+  asm("s_nop 1\n\t" BR_DPP("%0", "%0", "%1", "%2") : "+v"(f) : "v"(nl), "n"(L));
+}
+
 // g[v] += z[v](lane L of the row) * c for ten right-hand sides
 template <int L>
 __device__ __forceinline__ void row_rhs10(double* g, const double* z, double c) {

@@ -1,3 +1,4 @@
+// (Symmetric systems with 4 <= ncx <= 32 are solved in coarse_rows.hip.)
 // Batched coarse solve S U = b (Sec. 2.2 eq. upscaleSUF) with the
 // Petrov-Galerkin load (eq. stiffness_local_petrov), and the Monte Carlo
 // mean / variance of the coarse solution (Sec. 4.1.1).
@@ -26,7 +27,7 @@
 // cross-lane read, no memory round trip) and subtracts l_{j,i} x_j from the
 // z_i, i in [j-B, j), of every lane; the L entries are loaded a few steps
 // ahead, and the z values of the block after next one block ahead.
-#include "common.h"
+#include "coarse.h"
 
 namespace stomsfem {
 
@@ -56,16 +57,6 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-
-struct CoarseArgs {
-  int32_t ncx, ncy;
-  int64_t nsamples;
-  const double* S;
-  const double* load;
-  double* U;
-  int32_t* status;
-  double* work;  // nsamples * (nU * (ncx+1) + 1) doubles (one launch's samples)
-};
 
 // Entry of an element matrix with trial index tr and test index te: the
 // packed symmetric form, or the 16 row-major entries S[trial][test] of the
@@ -838,8 +829,8 @@ size_t coarse_lds_bytes(int ncx, bool pg) {
 int64_t coarse_grid(int64_t nsamples) { return nsamples < 4096 ? nsamples : 4096; }
 
 // Samples per launch: 4096 workgroups for the workgroup-per-sample kernels;
-// the one-lane-per-sample kernel of small square meshes takes up to 65536
-// (1024 wavefronts; its workspace is about 3.5 KB per sample).
+// square meshes up to 8 x 8 take up to 65536 (their workspace is about 3.5 KB
+// per sample).
 static int64_t coarse_chunk(int ncx, int ncy, int64_t nsamples) {
   const int64_t cap = (ncx == ncy && ncx <= 8) ? 65536 : 4096;
   return nsamples < cap ? nsamples : cap;
@@ -849,7 +840,7 @@ int64_t coarse_work_doubles(int ncx, int ncy, int64_t nsamples) {
   return coarse_chunk(ncx, ncy, nsamples) * ((int64_t)(ncx - 1) * (ncy - 1) * (ncx + 1) + 1);
 }
 
-// Small square coarse meshes (ncx = ncy = NC <= 8, the symmetric system):
+// The smallest square coarse meshes (ncx = ncy = NC <= 3, the symmetric system):
 // one lane per sample.  With NU = (NC-1)^2 unknowns and half-bandwidth
 // B = NC (couplings at offsets 1, NC-2, NC-1, NC), every row, window slot
 // and band offset is a compile-time constant, so the factor window lives in
@@ -987,16 +978,20 @@ static hipError_t launch_coarse_any(int ncx, int ncy, int64_t N, const double* S
       const int64_t n = N - c < chunk ? N - c : chunk;
       CoarseArgs a{ncx, ncy, n, S + c * (int64_t)ncx * ncy * ES, load, U + c * (int64_t)nU,
                    status ? status + c : nullptr, work};
-      if (!pg && ncx == ncy && ncx <= 8) {
+      // sixteen lanes per sample, window in registers: measured at 32 x 32,
+      // 1024 samples, 0.38 ms against 2.58 ms for the workgroup-per-sample
+      // kernel; at 8 x 8, 18 against 66 us (64 samples) and 204 against 331 us
+      // (65 536) for one lane per sample
+      if (!pg && coarse_rows_supports(ncx)) {
+        hipError_t e = launch_coarse_rows(a, st);
+        if (e != hipSuccess) return e;
+        continue;
+      }
+      if (!pg && ncx == ncy && ncx <= 3) {
         // one lane per sample (the workspace holds n (nU (ncx+1) + 1) doubles)
         switch (ncx) {
           case 2: launch_lane<2>(a, st); break;
-          case 3: launch_lane<3>(a, st); break;
-          case 4: launch_lane<4>(a, st); break;
-          case 5: launch_lane<5>(a, st); break;
-          case 6: launch_lane<6>(a, st); break;
-          case 7: launch_lane<7>(a, st); break;
-          default: launch_lane<8>(a, st); break;
+          default: launch_lane<3>(a, st); break;
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1010,10 +1005,8 @@ static hipError_t launch_coarse_any(int ncx, int ncy, int64_t N, const double* S
           else
             hipLaunchKernelGGL((coarse_solve_kernel<16, true, 64>), grid, block, lds, st, a);
         } else {
-          if (need <= 2)
-            hipLaunchKernelGGL((coarse_solve_kernel<2, false, 64>), grid, block, lds, st, a);
-          else
-            hipLaunchKernelGGL((coarse_solve_kernel<9, false, 64>), grid, block, lds, st, a);
+          // ncx = 2 and 3 with ncy != ncx
+          hipLaunchKernelGGL((coarse_solve_kernel<2, false, 64>), grid, block, lds, st, a);
         }
       } else if (pg) {
         hipLaunchKernelGGL((coarse_solve_kernel<4, true, COARSE_THREADS>), grid, block, lds, st, a);

@@ -65,3 +65,30 @@ def test_oversampled_kernels_match_oracle(orc, m, o, dtype):
     S_ref = orc.upscale_os(a.astype(np.float64), 3, 3, m, o)[0].reshape(S.shape)
     assert (status.cpu().numpy() == 0).all()
     assert (np.abs(S - S_ref).max(-1) / np.abs(S_ref).max(-1)).max() < STOL
+
+
+@pytest.mark.parametrize("ncx,ncy", [(4, 4), (4, 2), (5, 9), (8, 8), (9, 17), (15, 3), (16, 2), (17, 17), (18, 5),
+                                     (20, 20), (31, 31), (32, 32), (32, 3)])
+@pytest.mark.parametrize("N", [1, 6])
+def test_coarse_rows_match_oracle(orc, ncx, ncy, N):
+    # bandwidths around the 16-row blocks, unknowns that fill the last panel or
+    # not, sample counts that are not a multiple of a wavefront's four; the last
+    # sample of six has an indefinite element and is flagged alone
+    from paper_1607_00693_amd import stomsfem as sm
+
+    print(f"[rows] coarse {ncx}x{ncy} N={N}", flush=True)
+    a = W.lognormal_field((N, ncy * 2, ncx * 2), 1.0, 700 + 40 * ncx + ncy)
+    S = orc.upscale(a, ncx, ncy, 2)[0]
+    load = W.uniform_array((ncx * ncy, 4), 0.0, 1.0, 79)
+    Sd = torch.from_numpy(S).cuda()
+    status = torch.full((N,), 7, dtype=torch.int32, device="cuda")
+    for lv in (None, load):
+        U, _, _ = sm.coarse_solve(Sd, ncx, ncy, load=None if lv is None else torch.from_numpy(lv).cuda(), status=status)
+        ref = orc.coarse_solve(S, ncx, ncy, load_vec=lv)[0]
+        assert (status.cpu().numpy() == 0).all()
+        assert (np.linalg.norm(U.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)).max() < STOL
+    if N == 6:
+        Sd[5] *= -1.0
+        V, _, _ = sm.coarse_solve(Sd, ncx, ncy, load=torch.from_numpy(load).cuda(), status=status)
+        assert list(status.cpu().numpy() != 0) == [False] * 5 + [True]
+        assert (V[:5].cpu() == U[:5].cpu()).all()
