@@ -97,6 +97,22 @@ struct BumpParams {
   double rho, eps, base, amp, beta;
 };
 
+// sqrt psi_j at (x, y) of the bump centred in cell (jx, jy): 1 - |x - c_j|^2 /
+// rho^2, or 0 outside the disc.  Every kernel that forms the family's
+// coefficient takes it, the sum (in increasing j, terms fma(xi_j q, q, sum))
+// and the oscillating factor in these roundings, so that a coefficient
+// regenerated for one element is the generated field's bit for bit.
+__device__ __forceinline__ double bump_root(double x, double y, int jx, int jy, double ginv, double rinv2) {
+#pragma clang fp contract(off)
+  const double dx = __builtin_fma(-ginv, jx + 0.5, x), dy = __builtin_fma(-ginv, jy + 0.5, y);
+  const double r2 = __builtin_fma(dx, dx, dy * dy) * rinv2;
+  return r2 < 1.0 ? 1.0 - r2 : 0.0;
+}
+__device__ __forceinline__ double bump_osc(const BumpParams& bp, double sx, double sy) {
+#pragma clang fp contract(off)
+  return __builtin_fma(bp.amp * sx, sy, bp.base);
+}
+
 // sum_j xi_j psi_j(x, y) of the bump family at the point (x, y), xs = this
 // sample's xi.  Only bumps whose centre cell lies within ceil(rho*g) cells
 // are visited, in increasing index order.
@@ -112,14 +128,31 @@ __device__ __forceinline__ double bump_field_cell(double x, double y, const doub
   const double ginv = 1.0 / bp.g, rinv2 = 1.0 / (bp.rho * bp.rho);
   const int reach = (int)ceil(bp.rho * bp.g);
   double field = 0.0;
-  for (int jy = max(by - reach, 0); jy <= min(by + reach, bp.g - 1); ++jy) {
-    const double cy = (jy + 0.5) * ginv, dy2 = (y - cy) * (y - cy);
+  for (int jy = max(by - reach, 0); jy <= min(by + reach, bp.g - 1); ++jy)
     for (int jx = max(bx - reach, 0); jx <= min(bx + reach, bp.g - 1); ++jx) {
-      const double cx = (jx + 0.5) * ginv;
-      const double r2 = ((x - cx) * (x - cx) + dy2) * rinv2;
-      if (r2 < 1.0) field += xs[(jy * bp.g + jx) * XS] * (1.0 - r2) * (1.0 - r2);
+      const double q = bump_root(x, y, jx, jy, ginv, rinv2);
+      if (q > 0.0) field = __builtin_fma(xs[(jy * bp.g + jx) * XS] * q, q, field);
     }
+  return field;
+}
+
+// The same where the discs reach one cell at most (ceil(rho g) <= 1): the nine
+// candidates unrolled, so that their loads and bump values overlap instead of
+// following one another through the loop.
+__device__ __forceinline__ double bump_field_near(double x, double y, const double* xs, const BumpParams& bp, int bx,
+                                                  int by) {
+  const double ginv = 1.0 / bp.g, rinv2 = 1.0 / (bp.rho * bp.rho);
+  double xi[9], q[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int jx = bx + k % 3 - 1, jy = by + k / 3 - 1;
+    const bool in = jx >= 0 && jx < bp.g && jy >= 0 && jy < bp.g;
+    xi[k] = xs[in ? jy * bp.g + jx : by * bp.g + bx];
+    q[k] = in ? bump_root(x, y, jx, jy, ginv, rinv2) : 0.0;
   }
+  double field = 0.0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) field = q[k] > 0.0 ? __builtin_fma(xi[k] * q[k], q[k], field) : field;
   return field;
 }
 
@@ -141,7 +174,7 @@ __device__ __forceinline__ double feature_theta(double xi, double decades) {
 // a(x, xi) of the bump family at the point (x, y).
 __device__ __forceinline__ double bump_coef(double x, double y, const double* xs, const BumpParams& bp) {
   const double field = bump_field(x, y, xs, bp);
-  const double osc = bp.base + bp.amp * sin(2.0 * M_PI * x / bp.eps) * sin(2.0 * M_PI * y / bp.eps);
+  const double osc = bump_osc(bp, sin(2.0 * M_PI * x / bp.eps), sin(2.0 * M_PI * y / bp.eps));
   return osc * exp(bp.beta * field);
 }
 

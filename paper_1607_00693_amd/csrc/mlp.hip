@@ -804,8 +804,8 @@ __global__ void zero_u64_kernel(unsigned long long* p, int n) {
   if (i < n) p[i] = 0ull;
 }
 
-// Plain solve of the listed pairs (m = 8), coefficients regenerated from xi,
-// one lane per pair.  The statistics are combined over the wavefront before
+// Plain solve of the listed pairs (m = 8), coefficients regenerated from xi.
+// The statistics are combined over the wavefront before
 // one atomic per counter.
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
 #pragma unroll
@@ -816,59 +816,69 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
   return v;
 }
 
+// Every wavefront takes an equal share of the list, up to FB_PAIRS at a time:
+// the coefficients of a pair are formed one element per lane, then a lane
+// solves a pair.  The registers of the solve leave one wavefront per SIMD, so
+// the launch has at most 1024 and its time is the latency of one wavefront's
+// stream (about 250 instructions per pair for the coefficients, 5000 for the
+// solves): 3% of 1 048 576 pairs in 60 us, against 97 us with one lane doing
+// a whole pair, its 64 coefficients included.
+constexpr int FB_PAIRS = 64, FB_SUB = 16, FB_WAVES = 1024;
+
 __global__ __launch_bounds__(64) void mlp_fallback_kernel(MlpInferArgs a) {
-  __shared__ double blk[64][64];  // one 8 x 8 coefficient block per lane
-  // each lane's sample's xi, staged in LDS (column per lane) when the family
-  // has at most XL of them: the bump sums over the 64 elements then read
-  // them from LDS instead of issuing a dependent global load per candidate
-  // bump; 40 KB per workgroup keeps four workgroups (one per SIMD) per CU
+  __shared__ double blk[FB_PAIRS][65];  // one 8 x 8 coefficient block per pair
+  // FB_SUB pairs' sample xi, when the family has at most XL of them, and the
+  // oscillation's sines of their element columns and rows
   constexpr int XL = 16;
-  __shared__ double xl[XL][64];
+  __shared__ double xl[FB_SUB][XL], sn[FB_SUB][16];
+  __shared__ int64_t ps[FB_PAIRS];
   const int lane = threadIdx.x;
   const unsigned long long count = *a.count;
   const double h = 1.0 / (a.ncx * 8);
   const BumpParams bp{a.bump_g, a.bump_rho, a.bump_eps, a.bump_base, a.bump_amp, a.bump_beta};
+  const int nb = bp.g * bp.g;
+  const bool near = bp.rho * bp.g <= 1.0;
+  const unsigned long long even = (count + gridDim.x - 1) / gridDim.x;
+  const unsigned long long share = even < FB_PAIRS ? (even > 0 ? even : 1) : FB_PAIRS;
   // wavefront-uniform loop: every lane takes part in the statistics
-  for (unsigned long long base = (unsigned long long)blockIdx.x * 64; base < count;
-       base += (unsigned long long)gridDim.x * 64) {
-    const unsigned long long idx = base + lane;
+  for (unsigned long long base = blockIdx.x * share; base < count; base += gridDim.x * share) {
+    const int np = (int)(count - base < share ? count - base : share);
+    wave_lds_sync();  // the previous pairs' readers
+    ps[lane] = a.list[base + (lane < np ? lane : 0)];
+#pragma unroll 1
+    for (int g0 = 0; g0 < np; g0 += FB_SUB) {
+      wave_lds_sync();
+#pragma unroll 1
+      for (int t = lane; t < FB_SUB * 16; t += 64) {
+        const int g = t >> 4, q = t & 7;
+        const int64_t s = ps[g0 + g] / a.npatch;
+        const int K = (int)(ps[g0 + g] - s * a.npatch);
+        const int k = (t & 8) ? K / a.ncx : K % a.ncx;
+        const double z = (k * 8 + q + 0.5) * h;
+        sn[g][t & 15] = sin(2.0 * M_PI * z / bp.eps);
+        if (nb <= XL && (t & 15) < nb) xl[g][t & 15] = a.xi[s * a.nxi + (t & 15)];
+      }
+      wave_lds_sync();
+      // the coefficient of each fine element, as the coefficient kernel forms
+      // it (same operations, so the same bits)
+      const int ex = lane & 7, ey = lane >> 3;
+      const int n = np - g0 < FB_SUB ? np - g0 : FB_SUB;
+#pragma unroll 1
+      for (int g = 0; g < n; ++g) {
+        const int64_t s = ps[g0 + g] / a.npatch;
+        const int K = (int)(ps[g0 + g] - s * a.npatch);
+        const double x = (K % a.ncx * 8 + ex + 0.5) * h, y = (K / a.ncx * 8 + ey + 0.5) * h;
+        const double* xs = nb <= XL ? &xl[g][0] : a.xi + s * a.nxi;
+        const double field = near ? bump_field_near(x, y, xs, bp, bump_cell(x, bp.g), bump_cell(y, bp.g))
+                                  : bump_field(x, y, xs, bp);
+        blk[g0 + g][lane] = bump_osc(bp, sn[g][ex], sn[g][8 + ey]) * exp(bp.beta * field);
+      }
+    }
+    wave_lds_sync();
     bool rejected = false, audited = false;
     double rel = 0.0;
-    if (idx < count) {
-      const int64_t p = a.list[idx];
-      const int64_t s = p / a.npatch;
-      const int K = (int)(p - s * a.npatch);
-      const int kx = K % a.ncx, ky = K / a.ncx;
-      // the coefficient of each fine element, as the coefficient kernel forms
-      // it (same operations, so the same bits); the oscillation's sines are
-      // shared by the element rows and columns of the patch
-      double sxv[8], syv[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double xq = (kx * 8 + q + 0.5) * h, yq = (ky * 8 + q + 0.5) * h;
-        sxv[q] = sin(2.0 * M_PI * xq / bp.eps);
-        syv[q] = sin(2.0 * M_PI * yq / bp.eps);
-      }
-      const double* xs = a.xi + s * a.nxi;
-      const int nb = bp.g * bp.g;
-      auto regen = [&](auto xsc, const double* src) {
-        constexpr int XS = decltype(xsc)::value;
-#pragma unroll
-        for (int ey = 0; ey < 8; ++ey)
-#pragma unroll
-          for (int ex = 0; ex < 8; ++ex) {
-            const double x = (kx * 8 + ex + 0.5) * h, y = (ky * 8 + ey + 0.5) * h;
-            const double field = bump_field<XS>(x, y, src, bp);
-            const double osc = bp.base + bp.amp * sxv[ex] * syv[ey];
-            blk[lane][8 * ey + ex] = osc * exp(bp.beta * field);
-          }
-      };
-      if (nb <= XL) {
-        for (int j = 0; j < nb; ++j) xl[j][lane] = xs[j];
-        regen(std::integral_constant<int, 64>{}, &xl[0][lane]);
-      } else {
-        regen(std::integral_constant<int, 1>{}, xs);
-      }
+    if (lane < np) {
+      const int64_t p = ps[lane];
       double Sp[10];
       int32_t st = 0;
       small_cell_solve<8, double>(&blk[lane][0], 8, Sp, &st);
@@ -959,11 +969,10 @@ hipError_t launch_mlp_infer(const MlpInferArgs& a, int mode, hipStream_t st) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.S || a.m != 8 || a.family != MLP_FAMILY_BUMPS) return e;
-  // the listed count is known only on the device: enough wavefronts for
-  // about 3% of the pairs in one pass, looping beyond that
-  int64_t blocks = (a.nsamples * a.npatch / 32 + 63) / 64;
-  if (blocks > 4096) blocks = 4096;
-  if (blocks < 1) blocks = 1;
+  // the listed count is known only on the device: one wavefront per SIMD,
+  // fewer where the pairs themselves are few
+  int64_t blocks = (a.nsamples * a.npatch + 31) / 32;
+  if (blocks > FB_WAVES) blocks = FB_WAVES;
   hipLaunchKernelGGL(mlp_fallback_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a);
   return hipGetLastError();
 }
