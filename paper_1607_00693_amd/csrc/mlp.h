@@ -1,4 +1,4 @@
-// Internal interface of the surrogate kernels (mlp.hip).
+// Internal interface of the surrogate kernels (mlp.hip, mlp_train.hip).
 #pragma once
 #include "common.h"
 

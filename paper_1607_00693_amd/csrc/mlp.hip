@@ -3,14 +3,9 @@
 // Per coarse element K: local random variables x (the xi_j whose mode
 // touches K, Sec. 3 eq. MsFEB2, zero padded to 4) -> 64 -> 64 -> 64 -> 2 x 10,
 // GELU (exact erf form), two output heads predicting the standardised 10
-// unique entries of S_K.  Trained on pairs produced by the plain path.
+// unique entries of S_K.  Trained on pairs produced by the plain path
+// (mlp_train.hip).
 //
-//   mlp_train_kernel<TRAIN>  FP32 forward / hand-written backward over a
-//                            minibatch of 32, one workgroup per patch; with
-//                            TRAIN the Adam update is applied to each
-//                            parameter by the thread that formed its
-//                            gradient, otherwise the raw gradient is written
-//                            (parity checks against the oracle).
 //   mlp_infer_mma_kernel<F16> matrix-core inference (FP32 accumulation,
 //                            activations kept in registers, tabulated GELU),
 //                            then the gate per pair: BF16 with three-term
@@ -32,13 +27,7 @@
 
 namespace stomsfem {
 
-
 __device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad_f(float z) {
-  const float Phi = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-  const float phi = expf(-0.5f * z * z) * 0.39894228040143268f;
-  return Phi + z * phi;
-}
 
 // network input of local variable value xi, and the output scale of a
 // (sample, patch): see MLP_FAMILY_FEATURES
@@ -54,195 +43,8 @@ __device__ __forceinline__ double mlp_out_scale(int family, double decades, cons
   return sc;
 }
 
-// ---------------------------------------------------------------------------
-// Training / gradients
-// ---------------------------------------------------------------------------
-constexpr int MB = MLP_BATCH;  // minibatch per step
 constexpr int WD = MLP_WIDTH;
 constexpr int NO = MLP_NOUT2;
-
-template <bool TRAIN>
-__global__ __launch_bounds__(256) void mlp_train_kernel(MlpTrainArgs a) {
-  const int K = blockIdx.x;
-  const int tid = threadIdx.x;
-  float* P = a.params + (int64_t)K * MLP_NP;
-  float* m1 = a.m1 ? a.m1 + (int64_t)K * MLP_NP : nullptr;
-  float* m2 = a.m2 ? a.m2 + (int64_t)K * MLP_NP : nullptr;
-  __shared__ float X[MB][MLP_KIN], Tg[MB][10];
-  __shared__ float H1[MB][WD], G1[MB][WD], H2[MB][WD], G2[MB][WD], H3[MB][WD], G3[MB][WD], D[MB][WD];
-  __shared__ float dY[MB][NO];
-  __shared__ float red[256];
-  float* W1 = P + MLP_OW1;
-  float* b1 = P + MLP_OB1;
-  float* W2 = P + MLP_OW2;
-  float* b2 = P + MLP_OB2;
-  float* W3 = P + MLP_OW3;
-  float* b3 = P + MLP_OB3;
-  float* W4 = P + MLP_OW4;
-  float* b4 = P + MLP_OB4;
-  const float bc1 = 0.9f, bc2 = 0.999f;
-
-  for (int step = 0; step < a.steps; ++step) {
-    const int64_t t = a.t0 + step + 1;  // Adam step count
-    const float corr1 = 1.0f - powf(bc1, (float)t), corr2 = 1.0f - powf(bc2, (float)t);
-    // minibatch
-    for (int i = tid; i < MB * (MLP_KIN + 10); i += 256) {
-      const int b = i / (MLP_KIN + 10), c = i % (MLP_KIN + 10);
-      int64_t idx;
-      if (a.xb) {
-        idx = b;
-      } else {
-        const int64_t pos = ((int64_t)(a.t0 + step) * MB + b) % a.ntrain;
-        idx = a.perm ? a.perm[pos] : pos;
-        idx = idx < 0 ? 0 : (idx >= a.ntrain ? a.ntrain - 1 : idx);  // a malformed perm cannot read out of bounds
-      }
-      if (c < MLP_KIN) {
-        X[b][c] = a.xb ? a.xb[((int64_t)K * MB + b) * MLP_KIN + c] : a.X[((int64_t)K * a.ntrain + idx) * MLP_KIN + c];
-      } else {
-        const int q = c - MLP_KIN;
-        Tg[b][q] = a.tb ? a.tb[((int64_t)K * MB + b) * 10 + q] : a.T[((int64_t)K * a.ntrain + idx) * 10 + q];
-      }
-    }
-    __syncthreads();
-    // forward
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float z = b1[j];
-#pragma unroll
-      for (int k = 0; k < MLP_KIN; ++k) z += X[b][k] * W1[k * WD + j];
-      H1[b][j] = gelu_f(z);
-      G1[b][j] = gelu_grad_f(z);
-    }
-    __syncthreads();
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float z = b2[j];
-      for (int k = 0; k < WD; ++k) z += H1[b][k] * W2[k * WD + j];
-      H2[b][j] = gelu_f(z);
-      G2[b][j] = gelu_grad_f(z);
-    }
-    __syncthreads();
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float z = b3[j];
-      for (int k = 0; k < WD; ++k) z += H2[b][k] * W3[k * WD + j];
-      H3[b][j] = gelu_f(z);
-      G3[b][j] = gelu_grad_f(z);
-    }
-    __syncthreads();
-    float lpart = 0.0f;
-    for (int i = tid; i < MB * NO; i += 256) {
-      const int b = i / NO, o = i % NO;
-      float y = b4[o];
-      for (int k = 0; k < WD; ++k) y += H3[b][k] * W4[k * NO + o];
-      const float r = y - Tg[b][o % 10];
-      lpart += r * r;
-      dY[b][o] = 2.0f * r / (float)(MB * NO);
-    }
-    red[tid] = lpart;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (tid < w) red[tid] += red[tid + w];
-      __syncthreads();
-    }
-    if (tid == 0 && a.loss) a.loss[K] = red[0] / (float)(MB * NO);
-    // backward; each parameter's gradient is formed by one thread
-    auto apply = [&](float* /*base*/, int idx, float gval) {
-      if (TRAIN) {
-        const float mm1 = bc1 * m1[idx] + (1.0f - bc1) * gval;
-        const float mm2 = bc2 * m2[idx] + (1.0f - bc2) * gval * gval;
-        m1[idx] = mm1;
-        m2[idx] = mm2;
-        P[idx] -= a.lr * (mm1 / corr1) / (sqrtf(mm2 / corr2) + 1e-8f);
-      } else {
-        a.grads[(int64_t)K * MLP_NP + idx] = gval;
-      }
-    };
-    // dZ3 = (dY W4^T) .* gelu'(Z3)
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float s = 0.0f;
-      for (int o = 0; o < NO; ++o) s += dY[b][o] * W4[j * NO + o];
-      D[b][j] = s * G3[b][j];
-    }
-    __syncthreads();
-    for (int i = tid; i < WD * NO + NO; i += 256) {
-      float gval = 0.0f;
-      if (i < WD * NO) {
-        const int k = i / NO, o = i % NO;
-        for (int b = 0; b < MB; ++b) gval += H3[b][k] * dY[b][o];
-        apply(P, MLP_OW4 + i, gval);
-      } else {
-        const int o = i - WD * NO;
-        for (int b = 0; b < MB; ++b) gval += dY[b][o];
-        apply(P, MLP_OB4 + o, gval);
-      }
-    }
-    __syncthreads();
-    // dZ2 = (dZ3 W3^T) .* gelu'(Z2)  -> stored in G3 (no longer needed)
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float s = 0.0f;
-      for (int o = 0; o < WD; ++o) s += D[b][o] * W3[j * WD + o];
-      G3[b][j] = s * G2[b][j];
-    }
-    __syncthreads();
-    for (int i = tid; i < WD * WD + WD; i += 256) {
-      float gval = 0.0f;
-      if (i < WD * WD) {
-        const int k = i / WD, o = i % WD;
-        for (int b = 0; b < MB; ++b) gval += H2[b][k] * D[b][o];
-        apply(P, MLP_OW3 + i, gval);
-      } else {
-        const int o = i - WD * WD;
-        for (int b = 0; b < MB; ++b) gval += D[b][o];
-        apply(P, MLP_OB3 + o, gval);
-      }
-    }
-    __syncthreads();
-    // dZ1 = (dZ2 W2^T) .* gelu'(Z1)  -> stored in D
-    for (int i = tid; i < MB * WD; i += 256) {
-      const int b = i / WD, j = i % WD;
-      float s = 0.0f;
-      for (int o = 0; o < WD; ++o) s += G3[b][o] * W2[j * WD + o];
-      D[b][j] = s * G1[b][j];
-    }
-    __syncthreads();
-    for (int i = tid; i < WD * WD + WD; i += 256) {
-      float gval = 0.0f;
-      if (i < WD * WD) {
-        const int k = i / WD, o = i % WD;
-        for (int b = 0; b < MB; ++b) gval += H1[b][k] * G3[b][o];
-        apply(P, MLP_OW2 + i, gval);
-      } else {
-        const int o = i - WD * WD;
-        for (int b = 0; b < MB; ++b) gval += G3[b][o];
-        apply(P, MLP_OB2 + o, gval);
-      }
-    }
-    for (int i = tid; i < MLP_KIN * WD + WD; i += 256) {
-      float gval = 0.0f;
-      if (i < MLP_KIN * WD) {
-        const int k = i / WD, o = i % WD;
-        for (int b = 0; b < MB; ++b) gval += X[b][k] * D[b][o];
-        apply(P, MLP_OW1 + i, gval);
-      } else {
-        const int o = i - MLP_KIN * WD;
-        for (int b = 0; b < MB; ++b) gval += D[b][o];
-        apply(P, MLP_OB1 + o, gval);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-hipError_t launch_mlp_train(const MlpTrainArgs& a, bool train, hipStream_t st) {
-  if (train)
-    hipLaunchKernelGGL(mlp_train_kernel<true>, dim3(a.npatch), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL(mlp_train_kernel<false>, dim3(a.npatch), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
 
 // Gather the local variables and standardised targets of the training set.
 __global__ void mlp_gather_kernel(MlpDataArgs d) {
