@@ -6,18 +6,19 @@
 // element centroids (the randomized spectral method: w_j = sqrt(2) (z_j1/l1,
 // z_j2/l2) has the normal law whose characteristic function is the
 // covariance, phi_j = 2 pi u_j), kappa = 0.1 + exp(beta).  Each term is a
-// plane wave, so along a column of centroids it is c_k = cos(theta_0 + k a)
-// with a = w_j2 h: one thread walks a strip of GF_RY rows of one column with
-// one sincos per term and a three-operation recurrence per row, Reinsch's
-// form of the cosine recurrence (d_{k+1} = d_k + lambda c_k, c_{k+1} = c_k +
-// d_{k+1}, lambda = -4 sin^2(a/2), d_1 = -2 sin(a/2) sin(theta_0 + a/2)),
-// which stays accurate as a -> 0 where the three-term form
-// c_{k+1} = 2 cos(a) c_k - c_{k-1} loses digits.  The angle is first reduced
-// to [-pi/2, pi/2]: with a = a' + pi (mod 2 pi), c_k = (-1)^k cos(theta_0 +
-// k a'), so such terms run the same recurrence on a' and add the odd rows
-// with a minus sign.  beta stays within 2.5e-14 of the direct cosines at 256
-// terms and 64-row strips.  A workgroup covers 64 columns x 4 strips of one
-// sample; the sample's terms are staged in LDS.
+// plane wave.  Along a column of centroids, from the middle row of a strip of
+// 2 K + 1 rows on, cos(theta -+ k a) = cos(theta) cos(k a) +- sin(theta) sin(k a)
+// with a = w_j2 h: a lane adds its column's cos(theta) cos(k a) and
+// sin(theta) sin(k a) to two sums per k, and their sum and difference are the
+// two rows - one multiply-add per value and term.  cos(k a) and sin(k a) depend
+// on the term only; they lie along the 16 lanes of a DPP row and reach the
+// multiply-adds by row broadcast.  theta of a strip is the column's angle
+// turned by w_j2 y of its middle row.  A workgroup covers 64 columns x 4 strips
+// of one sample and forms the sines and cosines of 16 terms at a time in LDS
+// (one pair per column, k and strip).  FP64 issue bounds it: 256 samples of
+// 256 x 256 with 256 terms took 0.63 ms with a sincos per column, strip and
+// term and a recurrence of three operations per row; now 0.30 ms, of which the
+// multiply-adds are 0.13 (65 of a term's 97 instructions per wavefront).
 //
 // Local KL (host): the patch covariance exp(-dx^2/l1^2 - dy^2/l2^2) on the
 // m x m centroids is the Kronecker product of two m x m matrices, so its
@@ -35,27 +36,66 @@
 #include <cmath>
 #include <vector>
 
-#include "common.h"
+#include "band_rows.h"
 
 namespace stomsfem {
 
 constexpr int GF_TX = 64;     // columns per workgroup, one per lane
 constexpr int GF_SY = 4;      // strips per workgroup, one per wavefront
-constexpr int GF_RY = 64;     // rows per strip
+constexpr int GF_CT = 16;     // terms staged at a time
 constexpr int GF_JMAX = 1024;  // spectral terms per sample
 constexpr int KL_KMAX = 16;    // local KL terms
 
+// cos and sin of t quarter turns: t - rint(t) is exact, and the Taylor series to
+// the 15th and 16th power on [-pi/4, pi/4] are within 6e-17 of the functions.
+// A fixed three dozen instructions; an angle in turns needs no reduction modulo
+// a rounded pi.
+__device__ __forceinline__ double2 gf_turn(double t) {
+  const double q = rint(t), x = (t - q) * (0.5 * M_PI), w = x * x;
+  double sn = -1.0 / 1307674368000.0;
+  sn = fma(sn, w, 1.0 / 6227020800.0);
+  sn = fma(sn, w, -1.0 / 39916800.0);
+  sn = fma(sn, w, 1.0 / 362880.0);
+  sn = fma(sn, w, -1.0 / 5040.0);
+  sn = fma(sn, w, 1.0 / 120.0);
+  sn = fma(sn, w, -1.0 / 6.0);
+  sn = fma(sn * w, x, x);
+  double cs = 1.0 / 20922789888000.0;
+  cs = fma(cs, w, -1.0 / 87178291200.0);
+  cs = fma(cs, w, 1.0 / 479001600.0);
+  cs = fma(cs, w, -1.0 / 3628800.0);
+  cs = fma(cs, w, 1.0 / 40320.0);
+  cs = fma(cs, w, -1.0 / 720.0);
+  cs = fma(cs, w, 1.0 / 24.0);
+  cs = fma(cs, w, -0.5);
+  cs = fma(cs, w, 1.0);
+  const int k = (int)(q - 4.0 * floor(0.25 * q));  // quadrant
+  const double c = (k & 1) ? sn : cs, s = (k & 1) ? cs : sn;
+  return make_double2((k == 1 || k == 2) ? -c : c, k >= 2 ? -s : s);
+}
+
+// sums[k] += table(lane k of the row) * v, k < K
+template <int K>
+__device__ __forceinline__ void gf_accumulate(double* sums, const double* table, double v) {
+#pragma unroll
+  for (int k = 0; k < K; k += 16) row_update<0, K < 16 ? K : 16>(sums + k, table[k / 16], v);
+}
+
+template <int K>
 __global__ __launch_bounds__(256) void gauss_field_kernel(int64_t nsamples, int nfine, int J,
                                                           const double* __restrict__ z,
                                                           const double* __restrict__ u, double l1, double l2,
                                                           double* __restrict__ beta, double* __restrict__ kappa,
                                                           int tiles_x, int tiles_y) {
-  __shared__ double2 ws[GF_JMAX];   // (w1, w2)
-  __shared__ double2 hs[GF_JMAX];   // (sin a'/2, cos a'/2), a' = w2 h reduced to [-pi/2, pi/2]
-  __shared__ double2 ps[GF_JMAX];   // (phi, sign of the odd rows)
+  constexpr int RY = 2 * K + 1, NT = (K + 15) / 16, LT = 16 * NT;
+  __shared__ double wx[GF_JMAX], wy[GF_JMAX], ph[GF_JMAX];  // w1 h, w2 h, phi of the sample's terms in quarter turns
+  __shared__ double2 cols[GF_CT][GF_TX];   // (cos, sin) of w1 x + phi
+  __shared__ double2 rows[GF_CT][LT];      // of (k + 1) a
+  __shared__ double2 mids[GF_CT][GF_SY];   // of w2 y of the strips' middle rows
   const int64_t tiles = (int64_t)tiles_x * tiles_y;
   const int64_t nblk = nsamples * tiles;
-  const double h = 1.0 / nfine, amp = sqrt(2.0 / J);
+  const double h = 1.0 / nfine, amp = sqrt(2.0 / J), r1 = sqrt(2.0) / l1 * (2.0 / M_PI) * h,
+               r2 = sqrt(2.0) / l2 * (2.0 / M_PI) * h;  // to quarter turns per element
   const int lane = threadIdx.x & 63, strip = threadIdx.x >> 6;
   for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
     const int64_t s = b / tiles;
@@ -63,48 +103,56 @@ __global__ __launch_bounds__(256) void gauss_field_kernel(int64_t nsamples, int 
     const int tx = tt % tiles_x, ty = tt / tiles_x;
     __syncthreads();  // the previous tile's readers are done
     for (int j = threadIdx.x; j < J; j += 256) {
-      const double w1 = sqrt(2.0) * z[(s * J + j) * 2] / l1;
-      const double w2 = sqrt(2.0) * z[(s * J + j) * 2 + 1] / l2;
-      const double al = remainder(w2 * h, 2.0 * M_PI);  // [-pi, pi]
-      const bool alt = fabs(al) > 0.5 * M_PI;
-      const double alp = alt ? al - copysign(M_PI, al) : al;
-      double snh, csh;
-      sincos(0.5 * alp, &snh, &csh);
-      ws[j] = make_double2(w1, w2);
-      hs[j] = make_double2(snh, csh);
-      ps[j] = make_double2(2.0 * M_PI * u[s * J + j], alt ? -1.0 : 1.0);
+      wx[j] = r1 * z[(s * J + j) * 2];
+      wy[j] = r2 * z[(s * J + j) * 2 + 1];
+      ph[j] = 4.0 * u[s * J + j];
     }
-    __syncthreads();
-    const int ix = tx * GF_TX + lane, iy0 = (ty * GF_SY + strip) * GF_RY;
-    const double x = (ix + 0.5) * h, y0 = (iy0 + 0.5) * h;
-    double acc[GF_RY];
+    double even[K], odd[K], mid = 0.0;
 #pragma unroll
-    for (int k = 0; k < GF_RY; ++k) acc[k] = 0.0;
-    for (int j = 0; j < J; ++j) {
-      const double2 w = ws[j], hh = hs[j], pp = ps[j];
-      double c, sn;
-      sincos(w.x * x + w.y * y0 + pp.x, &sn, &c);
-      acc[0] += c;
-      const double lam = -4.0 * hh.x * hh.x;
-      double d = -2.0 * hh.x * (sn * hh.y + c * hh.x);
-#pragma unroll
-      for (int k = 1; k < GF_RY; ++k) {
-        c += d;
-        acc[k] = (k & 1) ? __builtin_fma(pp.y, c, acc[k]) : acc[k] + c;
-        d = __builtin_fma(lam, c, d);
+    for (int k = 0; k < K; ++k) even[k] = odd[k] = 0.0;
+    for (int j0 = 0; j0 < J; j0 += GF_CT) {
+      const int nj = J - j0 < GF_CT ? J - j0 : GF_CT;
+      __syncthreads();  // the previous terms' readers are done
+      constexpr int PER = GF_TX + LT + GF_SY;
+      for (int i = threadIdx.x; i < nj * PER; i += 256) {
+        const int j = i / PER, e = i - j * PER;
+        const double base = e < GF_TX ? ph[j0 + j] : 0.0, w = e < GF_TX ? wx[j0 + j] : wy[j0 + j];
+        const double at = e < GF_TX ? tx * GF_TX + e + 0.5
+                          : e < GF_TX + LT ? e - GF_TX + 1
+                                           : (ty * GF_SY + e - GF_TX - LT) * RY + K + 0.5;
+        double2* to = e < GF_TX ? &cols[j][e] : e < GF_TX + LT ? &rows[j][e - GF_TX] : &mids[j][e - GF_TX - LT];
+        *to = gf_turn(fma(w, at, base));
       }
-    }
-    if (ix < nfine) {
+      __syncthreads();
+      for (int j = 0; j < nj; ++j) {
+        const double2 x = cols[j][lane], y = mids[j][strip];
+        const double c = x.x * y.x - x.y * y.y, sn = x.y * y.x + x.x * y.y;
+        double tc[NT], ts[NT];
 #pragma unroll
-      for (int k = 0; k < GF_RY; ++k) {
-        const int iy = iy0 + k;
-        if (iy < nfine) {
-          const double bv = amp * acc[k];
-          const int64_t o = (s * nfine + iy) * (int64_t)nfine + ix;
-          if (beta) beta[o] = bv;
-          kappa[o] = 0.1 + exp(bv);
+        for (int t = 0; t < NT; ++t) {
+          const double2 v = rows[j][16 * t + (lane & 15)];
+          tc[t] = v.x;
+          ts[t] = v.y;
         }
+        mid += c;
+        gf_accumulate<K>(even, tc, c);
+        gf_accumulate<K>(odd, ts, sn);
       }
+    }
+    const int ix = tx * GF_TX + lane, iym = (ty * GF_SY + strip) * RY + K;
+    auto put = [&](int iy, double v) {
+      if (ix < nfine && iy < nfine) {
+        const double bv = amp * v;
+        const int64_t o = (s * nfine + iy) * (int64_t)nfine + ix;
+        if (beta) beta[o] = bv;
+        kappa[o] = 0.1 + exp(bv);
+      }
+    };
+    put(iym, mid);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      put(iym - 1 - k, even[k] + odd[k]);
+      put(iym + 1 + k, even[k] - odd[k]);
     }
   }
 }
@@ -112,12 +160,30 @@ __global__ __launch_bounds__(256) void gauss_field_kernel(int64_t nsamples, int 
 hipError_t launch_gauss_field(int64_t nsamples, int nfine, int J, const double* z, const double* u, double l1,
                               double l2, double* beta, double* kappa, hipStream_t st) {
   if (J < 1 || J > GF_JMAX) return hipErrorInvalidValue;
-  const int tiles_x = (nfine + GF_TX - 1) / GF_TX, tiles_y = (nfine + GF_SY * GF_RY - 1) / (GF_SY * GF_RY);
+  // Strips of 65, 33 or 17 rows: per term a wavefront spends about a quarter of
+  // the sines and cosines (50 instructions for 64 + K + 4 angles in 64 lanes),
+  // 2 K + 1 multiply-adds and a dozen others; the strip with the least of that
+  // over the rows of the mesh, those past its edge included.
+  const int ks[3] = {32, 16, 8}, cost[3] = {97, 62, 46};
+  int best = 0, tiles_y = 0;
+  for (int i = 0; i < 3; ++i) {
+    const int rows = GF_SY * (2 * ks[i] + 1), t = (nfine + rows - 1) / rows;
+    if (i == 0 || t * cost[i] < tiles_y * cost[best]) {
+      best = i;
+      tiles_y = t;
+    }
+  }
+  const int tiles_x = (nfine + GF_TX - 1) / GF_TX;
   int64_t blocks = nsamples * (int64_t)tiles_x * tiles_y;
   if (blocks == 0) return hipSuccess;
   if (blocks > (1 << 20)) blocks = 1 << 20;
-  hipLaunchKernelGGL(gauss_field_kernel, dim3((unsigned)blocks), dim3(256), 0, st, nsamples, nfine, J, z, u, l1, l2,
-                     beta, kappa, tiles_x, tiles_y);
+  const dim3 g((unsigned)blocks), t(256);
+  if (best == 0)
+    hipLaunchKernelGGL(gauss_field_kernel<32>, g, t, 0, st, nsamples, nfine, J, z, u, l1, l2, beta, kappa, tiles_x, tiles_y);
+  else if (best == 1)
+    hipLaunchKernelGGL(gauss_field_kernel<16>, g, t, 0, st, nsamples, nfine, J, z, u, l1, l2, beta, kappa, tiles_x, tiles_y);
+  else
+    hipLaunchKernelGGL(gauss_field_kernel<8>, g, t, 0, st, nsamples, nfine, J, z, u, l1, l2, beta, kappa, tiles_x, tiles_y);
   return hipGetLastError();
 }
 
