@@ -176,9 +176,12 @@ __device__ __forceinline__ void inner_sum2(const table_t* T, double w, const dou
     inner_sum<NN, 2, NE>(T, w, c2, c3, acc);
 }
 
-template <int NN, int KV, int NE>
+// The share of part `part` of `PARTS`: every PARTS-th value of the slower
+// variables (with fewer than three variables part 0 takes all).
+template <int NN, int KV, int NE, int PARTS>
 __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_KMAX], double lo,
-                                        double hi, double (&acc)[NE]) {
+                                        double hi, double (&acc)[NE], int part) {
+  if (KV < 3 && part > 0) return;
   double c0[NN], c1[NN], c2[NN], c3[NN];
   // variables are consumed from the fastest: the last one pairs with c3
   if constexpr (KV >= 1) lobatto_basis<NN>(x[KV - 1], lo, hi, c3);
@@ -194,7 +197,7 @@ __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_K
   } else if constexpr (KV == 3) {
 #pragma unroll 1
     for (int d1 = 0; d1 < NN; ++d1) {
-      inner_sum2<NN, NE>(T + (int64_t)d1 * inner * NE, c1[0], c2, c3, acc);
+      if (d1 % PARTS == part) inner_sum2<NN, NE>(T + (int64_t)d1 * inner * NE, c1[0], c2, c3, acc);
       shift_down<NN>(c1);
     }
   } else {
@@ -205,7 +208,8 @@ __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_K
       for (int q = 0; q < NN; ++q) c1r[q] = c1[q];
 #pragma unroll 1
       for (int d1 = 0; d1 < NN; ++d1) {
-        inner_sum2<NN, NE>(T + (int64_t)(d0 * NN + d1) * inner * NE, c0[0] * c1r[0], c2, c3, acc);
+        if ((d0 * NN + d1) % PARTS == part)
+          inner_sum2<NN, NE>(T + (int64_t)(d0 * NN + d1) * inner * NE, c0[0] * c1r[0], c2, c3, acc);
         shift_down<NN>(c1r);
       }
       shift_down<NN>(c0);
@@ -213,43 +217,60 @@ __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_K
   }
 }
 
-// Grid: ceil(nsamples / 256) x npatch workgroups in one dimension, remapped
-// so that all workgroups of one patch run on the same XCD (workgroups are
-// dealt to the 8 XCDs round-robin), which keeps each table in one L2.
-template <int NN, int NE>
+// Grid: ceil(nsamples PARTS / 256) x npatch workgroups in one dimension,
+// remapped so that all workgroups of one patch run on the same XCD (workgroups
+// are dealt to the 8 XCDs round-robin), which keeps each table in one L2.  With
+// PARTS = 4 the four wavefronts of a workgroup share the table rows of the same
+// 64 samples and their sums are added in LDS.
+template <int NN, int NE, int PARTS>
 __global__ __launch_bounds__(256) void ri_apply_kernel(RiApplyArgs a, int64_t nblk_s, int64_t nwork) {
   const int64_t b = blockIdx.x;
   const int64_t per_xcd = (int64_t)gridDim.x / 8;
   const int64_t w = (b % 8) * per_xcd + b / 8;
   if (w >= nwork) return;
   const int K = (int)(w / nblk_s);
-  const int64_t s = (w - (int64_t)K * nblk_s) * 256 + threadIdx.x;
-  if (s >= a.nsamples) return;
+  constexpr int PER = 256 / PARTS;
+  const int part = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PER);
+  const int64_t s = (w - (int64_t)K * nblk_s) * PER + threadIdx.x % PER;
+  const bool on = s < a.nsamples;
+  if (PARTS == 1 && !on) return;
   const int k = a.nlv[K];
   double x[RI_KMAX] = {0.0, 0.0, 0.0, 0.0};
-  bool inside = true;
+  bool inside = on;
 #pragma unroll
   for (int i = 0; i < RI_KMAX; ++i)
-    if (i < k) {
+    if (i < k && on) {
       x[i] = a.xi[s * a.nxi + a.lv[K * RI_KMAX + i]];
       inside = inside && (x[i] >= a.lo && x[i] <= a.hi);
     }
   const int64_t p = s * a.npatch + K;
-  if (!inside) {
+  if (on && !inside && part == 0) {  // S and status are written by the plain solve
     const unsigned long long slot = atomicAdd(a.list_count, 1ull);
     a.list[slot] = p;
-    return;  // S and status are written by the plain solve
   }
+  if (PARTS == 1 && !inside) return;
   const table_t* T = (const table_t*)(a.table + a.off[K] * NE);
   double acc[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) acc[e] = 0.0;
   switch (k) {
-    case 0: ri_eval<NN, 0, NE>(T, x, a.lo, a.hi, acc); break;
-    case 1: ri_eval<NN, 1, NE>(T, x, a.lo, a.hi, acc); break;
-    case 2: ri_eval<NN, 2, NE>(T, x, a.lo, a.hi, acc); break;
-    case 3: ri_eval<NN, 3, NE>(T, x, a.lo, a.hi, acc); break;
-    default: ri_eval<NN, 4, NE>(T, x, a.lo, a.hi, acc); break;
+    case 0: ri_eval<NN, 0, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+    case 1: ri_eval<NN, 1, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+    case 2: ri_eval<NN, 2, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+    case 3: ri_eval<NN, 3, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+    default: ri_eval<NN, 4, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+  }
+  if constexpr (PARTS > 1) {
+    __shared__ double sums[PARTS - 1][NE][PER];
+    if (part > 0)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) sums[part - 1][e][threadIdx.x % PER] = acc[e];
+    __syncthreads();
+    if (part > 0 || !inside) return;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int q = 0; q < PARTS - 1; ++q) acc[e] += sums[q][e][threadIdx.x];
   }
   double* So = a.S + p * NE;
 #pragma unroll
@@ -283,18 +304,30 @@ hipError_t launch_zero_u64(unsigned long long* p, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int NN>
-static hipError_t launch_apply_nn(const RiApplyArgs& a, hipStream_t st) {
-  const int64_t nblk_s = (a.nsamples + 255) / 256;
+template <int NN, int PARTS>
+static hipError_t launch_apply_parts(const RiApplyArgs& a, hipStream_t st) {
+  const int64_t nblk_s = (a.nsamples * PARTS + 255) / 256;
   const int64_t nwork = nblk_s * a.npatch;
   const int64_t grid = (nwork + 7) / 8 * 8;
   if (a.ne == 16)
-    hipLaunchKernelGGL((ri_apply_kernel<NN, 16>), dim3((unsigned)grid), dim3(256), 0, st, a, nblk_s, nwork);
+    hipLaunchKernelGGL((ri_apply_kernel<NN, 16, PARTS>), dim3((unsigned)grid), dim3(256), 0, st, a, nblk_s, nwork);
   else if (a.ne == 0 || a.ne == 10)
-    hipLaunchKernelGGL((ri_apply_kernel<NN, 10>), dim3((unsigned)grid), dim3(256), 0, st, a, nblk_s, nwork);
+    hipLaunchKernelGGL((ri_apply_kernel<NN, 10, PARTS>), dim3((unsigned)grid), dim3(256), 0, st, a, nblk_s, nwork);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+// Up to two wavefronts of pairs per SIMD (one at five nodes or fewer, where the
+// unrolled rows of the single wavefront hide more) the table's scalar loads are
+// waited for: four wavefronts to a table row then.  One wavefront per SIMD: 7
+// nodes 247 -> 97 us, 5 nodes 60 -> 43; two: 221 -> 178 and 5 nodes 62 us alone;
+// four: 351 alone against 372, 5 nodes 103 against 125.
+template <int NN>
+static hipError_t launch_apply_nn(const RiApplyArgs& a, hipStream_t st) {
+  if constexpr (NN >= 4)
+    if ((a.nsamples + 63) / 64 * a.npatch <= (NN > 5 ? 2048 : 1024)) return launch_apply_parts<NN, 4>(a, st);
+  return launch_apply_parts<NN, 1>(a, st);
 }
 
 hipError_t launch_ri_apply(const RiApplyArgs& a, hipStream_t st) {
