@@ -39,7 +39,13 @@ struct PhiArgs {
   double* phi;  // [npairs][3][nI]
 };
 
-template <typename TA>
+// LDS latency and the issue of the band updates bound it; a lane's place in the
+// triangle below a pivot is worked out once (it took a square root per pivot),
+// and the backward pass spreads a solved value over the rows before it.  PHI_Q,
+// PHI_F: entries and right-hand sides of a pivot's update per lane, from m <= 10
+// (55 entries) and m <= 21 (63 right-hand sides) on.  16 384 pairs at m = 8:
+// 245 -> 119 us.
+template <typename TA, int PHI_Q, int PHI_F>
 __global__ __launch_bounds__(64) void cell_phi_kernel(PhiArgs pa) {
   extern __shared__ double smem[];
   const UpArgs& args = pa.up;
@@ -50,6 +56,22 @@ __global__ __launch_bounds__(64) void cell_phi_kernel(PhiArgs pa) {
   const int tid = threadIdx.x;
   const int Mc = args.ncx * args.ncy;
   const int64_t lda = (int64_t)args.ncx * m;
+  // this lane's entries (io, ko) of the triangle below a pivot, and its rows
+  // fi and right-hand sides fl
+  int io[PHI_Q], ko[PHI_Q], fi[PHI_F], fl[PHI_F];
+#pragma unroll
+  for (int k = 0; k < PHI_Q; ++k) {
+    const int q = tid + 64 * k;
+    int i = 0;
+    while ((i + 1) * (i + 2) / 2 <= q) ++i;
+    io[k] = i;
+    ko[k] = q - i * (i + 1) / 2;
+  }
+#pragma unroll
+  for (int k = 0; k < PHI_F; ++k) {
+    fi[k] = (tid + 64 * k) / 3;
+    fl[k] = (tid + 64 * k) % 3;
+  }
   for (int64_t p = blockIdx.x; p < args.npairs; p += gridDim.x) {
     const int64_t s = p / Mc;
     const int K = (int)(p - s * Mc);
@@ -83,36 +105,34 @@ __global__ __launch_bounds__(64) void cell_phi_kernel(PhiArgs pa) {
     __syncthreads();
     // right-looking LDL^T, column j kept unscaled (W_ij = l_ij d_j)
     for (int j = 0; j < nI; ++j) {
-      const double d = Bd[j * (B + 1)];
-      const double inv = 1.0 / d;
+      const double inv = 1.0 / Bd[j * (B + 1)];
       const int cnt = (j + B < nI - 1 ? j + B : nI - 1) - j;
-      const int npairs = cnt * (cnt + 1) / 2;
-      for (int q = tid; q < npairs; q += blockDim.x) {
-        int io = (int)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);
-        while (io * (io + 1) / 2 > q) --io;
-        while ((io + 1) * (io + 2) / 2 <= q) ++io;
-        const int ko = q - io * (io + 1) / 2;
-        const int i = j + 1 + io, k = j + 1 + ko;
-        Bd[i * (B + 1) + (i - k)] -= Bd[i * (B + 1) + (i - j)] * inv * Bd[k * (B + 1) + (k - j)];
-      }
-      for (int t = tid; t < 3 * cnt; t += blockDim.x) {
-        const int i = j + 1 + t / 3, l = t % 3;
-        F[l * nI + i] -= Bd[i * (B + 1) + (i - j)] * inv * F[l * nI + j];
+      double* next = Bd + (j + 1) * (B + 1);
+#pragma unroll
+      for (int k = 0; k < PHI_Q; ++k)
+        if (io[k] < cnt) {
+          const double *x = next + io[k] * (B + 1), *y = next + ko[k] * (B + 1);
+          next[io[k] * (B + 1) + io[k] - ko[k]] -= x[io[k] + 1] * inv * y[ko[k] + 1];
+        }
+#pragma unroll
+      for (int k = 0; k < PHI_F; ++k) {
+        const int t = tid + 64 * k, i = fi[k];
+        if (i < cnt && t < 3 * B) F[fl[k] * nI + j + 1 + i] -= next[i * (B + 1) + i + 1] * inv * F[fl[k] * nI + j];
       }
       __syncthreads();
     }
-    // backward: x_j = (y_j - sum_{t=1..B} W_{j+t,j} x_{j+t}) / d_j
-    if (tid < 3) {
-      double* x = F + tid * nI;
-      for (int j = nI - 1; j >= 0; --j) {
-        double v = x[j];
-        const int t1 = (j + B < nI - 1 ? j + B : nI - 1) - j;
-        for (int t = 1; t <= t1; ++t) v -= Bd[(j + t) * (B + 1) + t] * x[j + t];
-        x[j] = v / Bd[j * (B + 1)];
+    // backward, right looking: x_j = v_j / d_j (v stays), v_{j-t} -= W_{j,j-t} x_j
+    for (int j = nI - 1; j >= 0; --j) {
+      const double d = Bd[j * (B + 1)];
+#pragma unroll
+      for (int k = 0; k < PHI_F; ++k) {
+        const int t = tid + 64 * k, i = fi[k] + 1, l = fl[k];
+        if (t < 3 * B && i <= j) F[l * nI + j - i] -= Bd[j * (B + 1) + i] * (F[l * nI + j] / d);
       }
+      __syncthreads();
     }
     __syncthreads();
-    for (int i = tid; i < 3 * nI; i += blockDim.x) pa.phi[p * 3 * nI + i] = F[i];
+    for (int i = tid; i < 3 * nI; i += blockDim.x) pa.phi[p * 3 * nI + i] = F[i] / Bd[(i % nI) * (B + 1)];
   }
 }
 
@@ -121,27 +141,30 @@ size_t cell_phi_lds_bytes(int m) {
   return sizeof(double) * ((size_t)m * m + (size_t)nI * (m + 1) + 3 * (size_t)nI);
 }
 
+template <typename TA, int PHI_Q, int PHI_F>
+static hipError_t launch_phi(const PhiArgs& pa, unsigned blocks, size_t lds, hipStream_t st) {
+  // above 64 KB the kernel's dynamic-LDS limit is raised on the current
+  // device before the launch
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)cell_phi_kernel<TA, PHI_Q, PHI_F>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((cell_phi_kernel<TA, PHI_Q, PHI_F>), dim3(blocks), dim3(64), lds, st, pa);
+  return hipGetLastError();
+}
+
 hipError_t launch_cell_phi(const UpArgs& args, int a_dtype, double* phi, hipStream_t st) {
-  PhiArgs pa{args, phi};
+  const PhiArgs pa{args, phi};
   const int64_t blocks = args.npairs < 65536 ? args.npairs : 65536;
   if (blocks == 0) return hipSuccess;
   const size_t lds = cell_phi_lds_bytes(args.m);
   if (lds > CELL_PHI_LDS_MAX) return hipErrorInvalidValue;
-  // above 64 KB the kernel's dynamic-LDS limit is raised on the current
-  // device before the launch
-  hipError_t e = hipSuccess;
-  if (a_dtype == STOMSFEM_F32) {
-    if (lds > 65536)
-      e = hipFuncSetAttribute((const void*)cell_phi_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    if (e == hipSuccess) hipLaunchKernelGGL(cell_phi_kernel<float>, dim3((unsigned)blocks), dim3(64), lds, st, pa);
-  } else {
-    if (lds > 65536)
-      e = hipFuncSetAttribute((const void*)cell_phi_kernel<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    if (e == hipSuccess) hipLaunchKernelGGL(cell_phi_kernel<double>, dim3((unsigned)blocks), dim3(64), lds, st, pa);
-  }
-  return e != hipSuccess ? e : hipGetLastError();
+  const unsigned g = (unsigned)blocks;
+  const bool f32 = a_dtype == STOMSFEM_F32;
+  if (args.m <= 10) return f32 ? launch_phi<float, 1, 1>(pa, g, lds, st) : launch_phi<double, 1, 1>(pa, g, lds, st);
+  if (args.m <= 15) return f32 ? launch_phi<float, 2, 1>(pa, g, lds, st) : launch_phi<double, 2, 1>(pa, g, lds, st);
+  return f32 ? launch_phi<float, 6, 2>(pa, g, lds, st) : launch_phi<double, 6, 2>(pa, g, lds, st);
 }
 
 // Snapshots of cells whose band does not fit a workgroup's LDS (used for
@@ -374,27 +397,32 @@ __device__ __forceinline__ bool rb_small_solve(const T* v, int r, double S3[3][3
   return ok;
 }
 
-// FP64 reference online stage: one thread per pair, dot products with G64.
+// FP64 reference online stage: one thread per pair, the 64 samples of a
+// wavefront on one patch, so that the table is read at uniform addresses
+// (scalar loads): 65 536 pairs at m = 8 took 260 us with the lanes along the
+// patches, 66 gathers per coefficient; 55 us so.
+typedef __attribute__((address_space(4))) const double rb_table_t;
 template <int RMAX, typename TA>
-__global__ __launch_bounds__(64) void rb_apply_f64_kernel(RbApplyArgs ra) {
+__global__ __launch_bounds__(64) void rb_apply_f64_kernel(RbApplyArgs ra, int64_t nsamples, unsigned groups) {
   const UpArgs& args = ra.up;
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= args.npairs) return;
   const int m = args.m, Mc = args.ncx * args.ncy;
-  const int64_t s = p / Mc;
-  const int K = (int)(p - s * Mc);
+  const int K = (int)(blockIdx.x / groups);
+  const int64_t s = (int64_t)(blockIdx.x % groups) * 64 + threadIdx.x;
+  if (s >= nsamples) return;
+  const int64_t p = s * Mc + K;
   const TA* a = (const TA*)args.a + block_offset(s, K, args.ncx, args.ncy, m);
   const int64_t lda = (int64_t)args.ncx * m;
   constexpr int P = RMAX * (RMAX + 1) / 2 + 3 * RMAX + 6;
   double v[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) v[q] = 0.0;
-  const double* G = ra.G64 + (int64_t)K * ra.KD * ra.PP;
-  for (int e = 0; e < m * m; ++e) {
-    const double ae = ld(a, (e / m) * lda + (e % m));
+  const rb_table_t* G = (const rb_table_t*)(ra.G64 + (int64_t)K * ra.KD * ra.PP);
+  for (int ey = 0; ey < m; ++ey)
+    for (int ex = 0; ex < m; ++ex, G += ra.PP) {
+      const double ae = ld(a, ey * lda + ex);
 #pragma unroll
-    for (int q = 0; q < P; ++q) v[q] += ae * G[e * ra.PP + q];
-  }
+      for (int q = 0; q < P; ++q) v[q] += ae * G[q];
+    }
   double S3[3][3];
   const bool ok = rb_small_solve<RMAX, double>(v, ra.rK[K], S3);
   store_packed(args.S + p * 10, S3);
@@ -624,11 +652,12 @@ hipError_t launch_rb_apply(const RbApplyArgs& ra, int a_dtype, bool f64, hipStre
   if (u.npairs == 0) return hipSuccess;
   if (ra.rmax != 8) return hipErrorInvalidValue;
   if (f64) {
-    const int64_t blocks = (u.npairs + 63) / 64;
+    const int64_t Mc = (int64_t)u.ncx * u.ncy, n = u.npairs / Mc, groups = (n + 63) / 64;
+    const dim3 g((unsigned)(groups * Mc));
     if (a_dtype == STOMSFEM_F32)
-      hipLaunchKernelGGL((rb_apply_f64_kernel<8, float>), dim3((unsigned)blocks), dim3(64), 0, st, ra);
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, float>), g, dim3(64), 0, st, ra, n, (unsigned)groups);
     else
-      hipLaunchKernelGGL((rb_apply_f64_kernel<8, double>), dim3((unsigned)blocks), dim3(64), 0, st, ra);
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, double>), g, dim3(64), 0, st, ra, n, (unsigned)groups);
     return hipGetLastError();
   }
   if (ra.PP != 80 || ra.KD % RBA_KC != 0 || ra.KD < u.m * u.m) return hipErrorInvalidValue;

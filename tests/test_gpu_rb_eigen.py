@@ -1,6 +1,7 @@
 """The offline reduced basis at the edges of its eigen-solver: one unknown, 64
 and 66 columns (where a lane takes more of a column), 126 and 129 (where the
-matrix leaves LDS), primal and dual forms, and training sets of few distinct
+matrix leaves LDS), primal and dual forms, the cell sizes where a lane of the
+snapshot kernel takes more of a pivot (11, 16, 22), and training sets of few distinct
 samples (a Gram matrix of rank 3).
 
 Tolerances: r exact and the first eigenvalues within 1e-8 (1e-12 of the
@@ -20,7 +21,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize(
     "m,ntrain,distinct",
     [(2, 1, 1), (2, 3, 3), (3, 1, 1), (3, 2, 2), (5, 40, 40), (6, 20, 20), (9, 22, 22), (9, 64, 2), (10, 40, 40), (12, 21, 21),
-     (12, 22, 22), (12, 42, 42), (13, 42, 42), (13, 43, 43), (13, 50, 50), (13, 46, 2), (20, 16, 16)])
+     (12, 22, 22), (12, 42, 42), (13, 42, 42), (13, 43, 43), (13, 50, 50), (13, 46, 2), (20, 16, 16), (11, 8, 8), (15, 5, 5), (16, 5, 5), (21, 4, 4), (22, 4, 4),
+     (26, 3, 3)])
 def test_modes_match_oracle(m, ntrain, distinct):
     from oracle import core, rb
     from paper_1607_00693_amd import stomsfem as sm
