@@ -96,7 +96,7 @@ struct BackStep {
 
 // FAR: B may exceed 64, so indices two blocks down can be in [j-B, j)
 template <bool FAR>
-__device__ __forceinline__ BackStep back_loads(const double* Lc, int64_t zero, int WN, int B, int nU, int j,
+__device__ __forceinline__ BackStep back_loads(const double* Lc, int64_t zero, int WN, int B, int nU, int np, int j,
                                                int lam) {
   // every step issues the same loads (out-of-range steps read the zero), so
   // that the number of loads in flight behind any one of them is fixed
@@ -104,7 +104,8 @@ __device__ __forceinline__ BackStep back_loads(const double* Lc, int64_t zero, i
   const bool in = j >= 0 && j < nU;
   const int k = j >> 6, u = j & 63;
   const int dc = u - lam;  // offset j - i in block k; + 64 in block k-1, + 128 in block k-2
-  const bool oc = in && dc >= 1 && dc <= B, o1 = in && k >= 1 && dc + 64 <= B;
+  const int ic = 64 * k + lam;  // (columns from np on are no factors)
+  const bool oc = in && dc >= 1 && dc <= B && ic < np, o1 = in && k >= 1 && dc + 64 <= B && ic - 64 < np;
   const int64_t base = (int64_t)(64 * k + lam) * (WN - 1) + j;  // block k
   const int64_t step = (int64_t)64 * (WN - 1);
   r.lc = Lc[oc ? base : zero];
@@ -347,7 +348,13 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
 // Blocked forward pass for the symmetric system with 32 < B <= 64 (the
 // pivot-per-barrier kernel above is bound by the latency of its per-pivot
 // phase, not by arithmetic).  Panels of CB_NB pivots, 256 threads, one
-// barrier per panel, software-pipelined one panel deep:
+// barrier per panel, software-pipelined one panel deep.  The chain of panels is
+// what takes the time (1100 cycles per pivot), so a sample is eliminated from
+// both ends at once: one workgroup takes the first rows, one the last, as the
+// first rows of the domain turned by 180 degrees, and between B + 2 and B + 9
+// rows remain for coarse_middle_kernel.  256 samples of 64 x 64: 1.82 -> 1.06 ms,
+// the backward pass 0.53 -> 0.33.  Meshes of fewer than B + 18 rows take the
+// pivot-per-barrier kernel.
 //   wavefront 0 applies the rank-CB_NB update of panel P-1 to the columns of
 //      panel P, then factors panel P: every lane factors the CB_NB x CB_NB
 //      diagonal block (broadcast LDS reads, no cross-lane traffic) and
@@ -373,12 +380,36 @@ constexpr int CB_NB = 8;
 constexpr int CB_BMAX = 64;
 constexpr int CB_NE = (CB_BMAX * 10 + 63) / 64;  // element-row prefetch per lane of wavefront 2
 
+#define WAVE_FENCE() __threadfence_block()
+
 size_t coarse_blocked_lds_bytes(int ncx) {
   const int WN = ncx + 2 * CB_NB;
   return sizeof(double) * ((size_t)WN * (ncx + 1) + (size_t)WN + 3 * (size_t)ncx * 10);
 }
 
-__global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) {
+// Rows of the two halves and of the middle (see above).  The halves are whole
+// panels; the middle's columns of the workspace hold both windows, right-hand
+// sides and pivot flags, B^2 + 3 B + 2 values in at least B + 2 columns.
+struct CoarseSplit {
+  int top, bottom, mid;
+};
+__host__ __device__ inline CoarseSplit coarse_split(int B, int nU) {
+  CoarseSplit p;
+  p.top = (nU - B - 2) / (2 * CB_NB) * CB_NB;
+  p.bottom = (nU - B - 2 - p.top) / CB_NB * CB_NB;
+  p.mid = nU - p.top - p.bottom;
+  return p;
+}
+__host__ __device__ inline bool coarse_splits(int B, int nU) { return nU >= B + 2 + 2 * CB_NB; }
+
+// Packed entry q of an element matrix after a turn by 180 degrees (local nodes
+// 0 and 2, 1 and 3 change places).
+__device__ __forceinline__ int turned_entry(int q) {
+  constexpr unsigned long long T = 0x4106395287ull;  // digits 7 8 2 5 9 3 6 0 1 4, the first lowest
+  return (int)((T >> (4 * q)) & 15);
+}
+
+__global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs args) {
   constexpr int NB = CB_NB;
   extern __shared__ double smem[];
   const int ncx = args.ncx, ncy = args.ncy;
@@ -398,15 +429,20 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t s = blockIdx.x;
+  const int64_t s = blockIdx.x >> 1;
+  const int half = blockIdx.x & 1;  // 1: the domain turned by 180 degrees
   if (s >= args.nsamples) return;
+  const CoarseSplit split = coarse_split(B, nU);
+  const int np = half ? split.bottom : split.top;  // pivots
+  const int nr = np + B;                           // rows of the half
   const double* Ss = args.S + s * (int64_t)ncx * ncy * 10;
   double* Us = args.U + s * (int64_t)nU;
-  double* Lc = args.work + s * ((int64_t)nU * BW + 1);  // column j: [1/d_j, l_{j+1,j}, ..., l_{j+B,j}]
+  double* Ls = args.work + s * ((int64_t)nU * BW + 1);
+  double* Lc = Ls + (half ? (int64_t)(nU - np) * BW : 0);  // column j: [1/d_j, l_{j+1,j}, ..., l_{j+B,j}]
   const double H = 1.0 / ncx;
   double* jk = &junk[lane];
   if (tid == 0) {
-    Lc[(int64_t)nU * BW] = 0.0;
+    if (!half) Ls[(int64_t)nU * BW] = 0.0;
     bad = 0;
     zero1 = 0.0;
   }
@@ -430,8 +466,8 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
       if (4 * tr + a < TB && 4 * tc + b <= 4 * tr + a) tmask |= 1u << (4 * a + b);
 
   auto node_load = [&](int r) -> double {
-    if (r >= nU) return 0.0;
-    const int px = r % nix + 1, py = r / nix + 1;
+    if (r >= np) return 0.0;
+    const int rr = half ? nU - 1 - r : r, px = rr % nix + 1, py = rr / nix + 1;
     if (!args.load) return H * H;  // four elements, int_K p^l = H^2/4 each
     const double* L = args.load;
     return (L[((py - 1) * ncx + (px - 1)) * 4 + 2] + L[((py - 1) * ncx + px) * 4 + 3]) +
@@ -466,12 +502,18 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
     pa = (e == 4 && iy >= 1 && ix >= 1) ? sSW + 2 : pa;        // (0,2)
     v = (*pa + *pb) + (*pc + *pd);
   };
+  // value t of (turned) element row e
+  auto element = [&](int e, int t) -> double {
+    if (!half) return Ss[(int64_t)e * ncx * 10 + t];
+    const int ex = t / 10;
+    return Ss[((int64_t)(ncy - 1 - e) * ncx + (ncx - 1 - ex)) * 10 + turned_entry(t - 10 * ex)];
+  };
   double epre[CB_NE];
   auto erow_fetch = [&](int e) {  // wavefront 2
 #pragma unroll
     for (int k = 0; k < CB_NE; ++k) {
       const int t = lane + 64 * k;
-      epre[k] = (e < ncy && t < ncx * 10) ? Ss[(int64_t)e * ncx * 10 + t] : 0.0;
+      epre[k] = (e < ncy && t < ncx * 10) ? element(e, t) : 0.0;
     }
   };
   auto erow_store = [&](int e) {
@@ -485,7 +527,7 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
   // prologue: element rows 0..2, the cleared window, rows 0 .. NB+B-1 and
   // their rhs
   for (int e = 0; e < 3 && e < ncy; ++e)
-    for (int t = tid; t < ncx * 10; t += CB_TH) Ec[e * ncx * 10 + t] = Ss[(int64_t)e * ncx * 10 + t];
+    for (int t = tid; t < ncx * 10; t += CB_TH) Ec[e * ncx * 10 + t] = element(e, t);
   for (int i = tid; i < WN * BW; i += CB_TH) Wb[i] = 0.0;
   int eld = ncy - 1 < 2 ? ncy - 1 : 2;  // highest element row in the ring
   if (wave == 2) erow_fetch(eld + 1);
@@ -494,25 +536,25 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
     const int r = i / 5, e = i - 5 * r;
     int t;
     double v;
-    if (r < nU) {
+    if (r < nr) {
       nonzero(r, e, t, v);
-      if (r - t >= 0) Wb[r * BW + t] = v;
+      if (r - t >= 0 && r - t < np) Wb[r * BW + t] = v;
     }
   }
   for (int r = tid; r < NB + B; r += CB_TH)
-    if (r < nU) F[r] = node_load(r);
+    if (r < nr) F[r] = node_load(r);
   double fnext = (wave == 2 && lane < NB) ? node_load(NB + B + lane) : 0.0;
   __syncthreads();
 
   int sj = 0;  // slot of row j0
   for (int P = 0;; ++P) {
     const int j0 = P * NB;
-    if (j0 - NB >= nU) break;
+    if (j0 - NB >= np) break;
     const int cb = P & 1, pb = cb ^ 1;  // buffers of panels P and P-1
-    if (wave == 0 && j0 < nU) {
+    if (wave == 0 && j0 < np) {
       // rows R1 = j0 + lane and R2 = j0 + 64 + lane; entry (R, j0 + k) in x[k]
-      const bool h1 = lane < NB + B && j0 + lane < nU;
-      const bool h2 = 64 + lane < NB + B && j0 + 64 + lane < nU;
+      const bool h1 = lane < NB + B && j0 + lane < nr;
+      const bool h2 = 64 + lane < NB + B && j0 + 64 + lane < nr;
       const int s1 = wrapn(sj + lane), s2 = wrapn(sj + (64 + lane < NB + B ? 64 + lane : 0));
       double x1[NB], x2[NB];
 #pragma unroll
@@ -539,18 +581,15 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
       }
       // the diagonal block (rows and columns j0 .. j0 + NB - 1) and the rhs
       // of its rows in every lane: lanes 0 .. NB-1 hold the block rows, the
-      // other lanes read them back (same addresses: broadcast); rows past nU
-      // are an identity block so that no pivot is zero there
+      // other lanes read them back (same addresses: broadcast)
 #pragma unroll
       for (int k = 0; k < NB; ++k) *(lane < NB && k <= lane ? &Bk[lane][k] : jk) = x1[k];
       double blk[NB][NB], fb[NB];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        const bool in = j0 + i < nU;
 #pragma unroll
-        for (int k = 0; k <= i; ++k) blk[i][k] = in ? Bk[i][k] : (i == k ? 1.0 : 0.0);
-        const double v = *(in ? &F[wrapn(sj + i)] : jk);
-        fb[i] = in ? v : 0.0;
+        for (int k = 0; k <= i; ++k) blk[i][k] = Bk[i][k];
+        fb[i] = F[wrapn(sj + i)];
       }
       // every lane factors the block (right-looking, pivot order) and
       // carries its own two rows along: entry (R, j0 + k) receives the
@@ -565,7 +604,7 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
         inv = fma(fma(-d, inv, 1.0), inv, inv);
         inv = fma(fma(-d, inv, 1.0), inv, inv);
         dinv[pp] = inv;
-        if (j0 + pp < nU && !(d > 0.0)) bad = 1;
+        if (!(d > 0.0)) bad = 1;
         const double y = fb[pp];
         yv[pp] = y;
 #pragma unroll
@@ -621,7 +660,7 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
       unsigned vm = tmask;  // entries inside the triangle and the system
 #pragma unroll
       for (int a = 0; a < 4; ++a)
-        if (j0 + NB + 4 * tr + a >= nU) vm &= ~(15u << (4 * a));
+        if (j0 + NB + 4 * tr + a >= nr) vm &= ~(15u << (4 * a));
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const int sa = wrapn(sj + NB + 4 * tr + a) * BW + 4 * (tr - tc) + a;  // slot(i) BW + (i - k) for b = 0
@@ -655,9 +694,9 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
       // rhs of the new rows (prefetched a step ahead); element ring: the
       // rows assembled in the next step need element rows up to
       // iy(last) + 1, and the slot written here holds a row no longer read
-      if (lane < NB && rb + lane < nU) F[wrapn(so + lane)] = fnext;
+      if (lane < NB && rb + lane < nr) F[wrapn(so + lane)] = fnext;
       fnext = lane < NB ? node_load(rb + lane + NB) : 0.0;
-      const int rl = j0 + 3 * NB + B - 1 < nU - 1 ? j0 + 3 * NB + B - 1 : nU - 1;
+      const int rl = j0 + 3 * NB + B - 1 < nr - 1 ? j0 + 3 * NB + B - 1 : nr - 1;
       if (rl / nix + 1 > eld && eld + 1 < ncy) {
         erow_store(eld + 1);
         ++eld;
@@ -667,19 +706,16 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
       if (P >= 1) {
         // columns j0 - NB .. j0 - 1 of L (a contiguous block of the
         // workspace) and their z
-        const int jp = j0 - NB, ncol = nU - jp < NB ? nU - jp : NB;
+        const int jp = j0 - NB;
         double* Lb = Lc + (int64_t)jp * BW;
 #pragma unroll
-        for (int pp = 0; pp < NB; ++pp) {
-          if (pp < ncol) {
-            for (int t = lane; t < BW; t += 64) {
-              const double* src =
-                  t == 0 ? &dq[pb][pp] : (t < NB - pp ? &Lq[pb][pp][pp + t] : &Lp[pb][pp][t - (NB - pp)]);
-              Lb[pp * BW + t] = *src;
-            }
+        for (int pp = 0; pp < NB; ++pp)
+          for (int t = lane; t < BW; t += 64) {
+            const double* src =
+                t == 0 ? &dq[pb][pp] : (t < NB - pp ? &Lq[pb][pp][pp + t] : &Lp[pb][pp][t - (NB - pp)]);
+            Lb[pp * BW + t] = *src;
           }
-        }
-        if (lane < ncol) Us[jp + lane] = zq[pb][lane];
+        if (lane < NB) Us[half ? nU - 1 - (jp + lane) : jp + lane] = zq[pb][lane];
       }
       // panel P-1's row slots: cleared, then the nonzeros of the rows first
       // touched by panel P+1 (LDS operations of one wavefront complete in
@@ -693,32 +729,143 @@ __global__ __launch_bounds__(CB_TH) void coarse_blocked_kernel(CoarseArgs args) 
         const int q = lane / 5, r = rb + q;
         int t = 0;
         double v = 0.0;
-        if (r < nU) nonzero(r, lane - 5 * q, t, v);
-        *(r < nU && r - t >= 0 ? &Wb[wrapn(so + q) * BW + t] : jk) = v;
+        if (r < nr) nonzero(r, lane - 5 * q, t, v);
+        *(r < nr && r - t >= 0 && r - t < np ? &Wb[wrapn(so + q) * BW + t] : jk) = v;
       }
     }
     sj = wrapn(sj + NB);
     COARSE_SYNC();
   }
+  // what the half adds to the matrix and right-hand side of the middle's B rows
+  // next to it; the last panel's update of its first NB columns is still to come
+  double* out = Ls + (int64_t)split.top * BW + half * (B * (B + 1) / 2 + B + 1);
+  const int lb = (np / NB - 1) & 1, sn = np % WN;
+  for (int i = wave; i < B; i += CB_TH / 64)
+    for (int c = lane; c <= i; c += 64) {
+      double v = Wb[wrapn(sn + i) * BW + i - c];
+      if (c < NB)
+        for (int pp = 0; pp < NB; ++pp) v -= Lp[lb][pp][i] * Ap[lb][pp][c];
+      out[i * (i + 1) / 2 + c] = v;
+    }
+  for (int i = tid; i < B; i += CB_TH) out[B * (B + 1) / 2 + i] = F[wrapn(sn + i)];
+  if (tid == 0) out[B * (B + 1) / 2 + B] = bad ? 1.0 : 0.0;
+}
+
+// The middle of the split: its own matrix and right-hand side, assembled, plus
+// what the two halves left, as a dense matrix in LDS (at most CB_BMAX + CB_NB + 1
+// rows), LDL^T and both substitutions.  256 samples of 64 x 64:
+// 84 us, a barrier and a division per pivot.
+constexpr int CM_N = CB_BMAX + CB_NB + 1, CM_LD = CM_N + 1;
+__global__ __launch_bounds__(CB_TH) void coarse_middle_kernel(CoarseArgs args) {
+  __shared__ double M[CM_N * CM_LD], G[CM_N];
+  __shared__ int bad;
+  const int ncx = args.ncx, ncy = args.ncy, nix = ncx - 1, nU = nix * (ncy - 1), B = ncx, BW = B + 1;
+  const int64_t s = blockIdx.x;
+  if (s >= args.nsamples) return;
+  const CoarseSplit split = coarse_split(B, nU);
+  const int n = split.mid, tid = threadIdx.x;
+  const double* Ss = args.S + s * (int64_t)ncx * ncy * 10;
+  const double* W0 = args.work + s * ((int64_t)nU * BW + 1) + (int64_t)split.top * BW;
+  const double* W1 = W0 + B * (B + 1) / 2 + B + 1;
+  double* Us = args.U + s * (int64_t)nU + split.top;
+  const double H = 1.0 / ncx;
+  if (tid == 0) bad = W0[B * (B + 1) / 2 + B] != 0.0 || W1[B * (B + 1) / 2 + B] != 0.0;
+  for (int i = tid; i < n * CM_LD; i += CB_TH) M[i] = 0.0;
+  __syncthreads();
+  for (int t = tid; t < 5 * n; t += CB_TH) {
+    const int i = t / 5, e = t - 5 * i, r = split.top + i, ix = r % nix, iy = r / nix;
+    // elements around the node: column ix or ix + 1, row iy or iy + 1
+    auto S = [&](int dx, int dy, int q) { return Ss[((int64_t)(iy + dy) * ncx + ix + dx) * 10 + q]; };
+    double v = 0.0;
+    int k = i;
+    if (e == 0) {
+      v = (S(0, 0, 7) + S(1, 0, 9)) + (S(0, 1, 4) + S(1, 1, 0));
+    } else if (e == 1) {
+      k = i - 1;
+      if (ix >= 1) v = S(0, 0, 8) + S(0, 1, 1);
+    } else if (e == 2) {
+      k = i - (nix - 1);
+      if (iy >= 1 && ix <= nix - 2) v = S(1, 0, 6);
+    } else if (e == 3) {
+      k = i - nix;
+      if (iy >= 1) v = S(0, 0, 5) + S(1, 0, 3);
+    } else {
+      k = i - (nix + 1);
+      if (iy >= 1 && ix >= 1) v = S(0, 0, 2);
+    }
+    if (k >= 0 && v != 0.0) M[i * CM_LD + k] = v;
+    if (e == 0) {
+      double f = H * H;
+      if (args.load) {
+        const double* L = args.load;
+        f = (L[(iy * ncx + ix) * 4 + 2] + L[(iy * ncx + ix + 1) * 4 + 3]) +
+            (L[((iy + 1) * ncx + ix) * 4 + 1] + L[((iy + 1) * ncx + ix + 1) * 4 + 0]);
+      }
+      G[i] = f;
+    }
+  }
+  __syncthreads();
+  for (int i = tid >> 6; i < B; i += CB_TH / 64)
+    for (int k = tid & 63; k <= i; k += 64) M[i * CM_LD + k] += W0[i * (i + 1) / 2 + k];
+  for (int i = tid; i < B; i += CB_TH) G[i] += W0[B * (B + 1) / 2 + i];
+  __syncthreads();
+  for (int i = tid >> 6; i < B; i += CB_TH / 64)
+    for (int k = tid & 63; k <= i; k += 64) M[(n - 1 - k) * CM_LD + n - 1 - i] += W1[i * (i + 1) / 2 + k];
+  for (int i = tid; i < B; i += CB_TH) G[n - 1 - i] += W1[B * (B + 1) / 2 + i];
+  __syncthreads();
+  // LDL^T, column j kept unscaled; row n of a thread's share is the right-hand side
+  const int tx = tid & 15, ty = tid >> 4;
+  for (int j = 0; j < n; ++j) {
+    const double d = M[j * CM_LD + j], inv = 1.0 / d, y = G[j];
+    if (tid == 0 && !(d > 0.0)) bad = 1;
+    for (int i = j + 1 + ty; i < n; i += 16) {
+      const double l = M[i * CM_LD + j] * inv;
+      for (int k = j + 1 + tx; k <= i; k += 16) M[i * CM_LD + k] -= l * M[k * CM_LD + j];
+      if (tx == 0) G[i] -= l * y;
+    }
+    __syncthreads();
+  }
+  // x_j = (y_j - sum_{i>j} w_ij x_i) / d_j: one wavefront, a solved value
+  // taken to the rows before it
+  if (tid < 64) {
+    for (int j = n - 1; j >= 0; --j) {
+      const double x = G[j] / M[j * CM_LD + j];
+      WAVE_FENCE();
+      if (tid == 0) G[j] = x;
+      for (int k = tid; k < j; k += 64) G[k] -= M[j * CM_LD + k] * x;
+      WAVE_FENCE();
+    }
+    for (int i = tid; i < n; i += 64) Us[i] = G[i];
+  }
   if (tid == 0 && args.status) args.status[s] = bad ? STOMSFEM_ENOTSPD : STOMSFEM_OK;
 }
 
+
 // Backward substitution L^T x = z for the samples of one forward launch: one
 // wavefront per sample (workgroup slice blockIdx.x of the workspace).
-template <bool FAR>
+// SPLIT: one wavefront per half of a split sample (coarse_blocked_kernel): rows
+// np .. np + B - 1 of the half are the middle's, solved already; they are taken
+// to the columns before them like the others.
+template <bool FAR, bool SPLIT = false>
 __global__ __launch_bounds__(64) void coarse_back_kernel(CoarseArgs args) {
   const int ncx = args.ncx, ncy = args.ncy;
-  const int nU = (ncx - 1) * (ncy - 1), B = ncx, WN = B + 1;
-  const int64_t s = blockIdx.x;
+  const int nS = (ncx - 1) * (ncy - 1), B = ncx, WN = B + 1;
+  const int64_t s = SPLIT ? blockIdx.x >> 1 : blockIdx.x;
   if (s >= args.nsamples) return;
-  const double* Lc = args.work + s * ((int64_t)nU * WN + 1);
-  const int64_t zero = (int64_t)nU * WN;
-  double* Us = args.U + s * (int64_t)nU;
+  const bool turned = SPLIT && (blockIdx.x & 1);
+  const CoarseSplit split = coarse_split(B, nS);
+  const int np = !SPLIT ? nS : turned ? split.bottom : split.top;
+  const int nU = SPLIT ? np + B : nS;  // rows
+  const int64_t first = turned ? (int64_t)(nS - np) * WN : 0;
+  const double* Lc = args.work + s * ((int64_t)nS * WN + 1) + first;
+  const int64_t zero = (int64_t)nS * WN - first;
+  double* Us = args.U + s * (int64_t)nS;
+  auto at = [&](int i) { return turned ? nS - 1 - i : i; };
   const int lam = threadIdx.x;
   const int kt = (nU - 1) >> 6;
   auto yload = [&](int k) -> double {
     const int i = 64 * k + lam;
-    return (k >= 0 && i < nU) ? Us[i] : 0.0;
+    return (k >= 0 && i < nU) ? Us[at(i)] : 0.0;
   };
   // yc, y1, y2: blocks k, k-1, k-2 (y2 only if FAR); yp: the next block to
   // enter, loaded one block ahead
@@ -726,7 +873,7 @@ __global__ __launch_bounds__(64) void coarse_back_kernel(CoarseArgs args) {
   double yp = yload(FAR ? kt - 3 : kt - 2);
   BackStep pf[COARSE_PD];
 #pragma unroll
-  for (int d = 0; d < COARSE_PD; ++d) pf[d] = back_loads<FAR>(Lc, zero, WN, B, nU, 64 * kt + 63 - d, lam);
+  for (int d = 0; d < COARSE_PD; ++d) pf[d] = back_loads<FAR>(Lc, zero, WN, B, nU, np, 64 * kt + 63 - d, lam);
   for (int k = kt; k >= 0; --k) {
     double xs = 0.0;
     // groups of COARSE_PD steps; step j issues the loads of step
@@ -745,11 +892,11 @@ __global__ __launch_bounds__(64) void coarse_back_kernel(CoarseArgs args) {
           if (FAR) y2 = __builtin_fma(-pf[d].l2, x, y2);
         }
         // the slot is free again: load step j - COARSE_PD into it
-        pf[d] = back_loads<FAR>(Lc, zero, WN, B, nU, j - COARSE_PD, lam);
+        pf[d] = back_loads<FAR>(Lc, zero, WN, B, nU, np, j - COARSE_PD, lam);
         __asm__ volatile("" ::: "memory");
       }
     }
-    if (64 * k + lam < nU) Us[64 * k + lam] = xs;
+    if (64 * k + lam < np) Us[at(64 * k + lam)] = xs;
     yc = y1;
     if (FAR) {
       y1 = y2;
@@ -1063,14 +1210,20 @@ static hipError_t launch_coarse_any(int ncx, int ncy, int64_t N, const double* S
         }
       } else if (pg) {
         hipLaunchKernelGGL((coarse_solve_kernel<4, true, COARSE_THREADS>), grid, block, lds, st, a);
-      } else if (use_blocked(ncx, pg)) {
+      } else if (use_blocked(ncx, pg) && coarse_splits(ncx, nU)) {
         // the kernel's dynamic-LDS limit raised before each launch (a host call;
         // it then holds on whichever device is current)
         const hipError_t attr = hipFuncSetAttribute((const void*)coarse_blocked_kernel,
                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                                     (int)coarse_blocked_lds_bytes(CB_BMAX));
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(coarse_blocked_kernel, grid, dim3(CB_TH), lds, st, a);
+        const dim3 halves((unsigned)(2 * n));
+        hipLaunchKernelGGL(coarse_blocked_kernel, halves, dim3(CB_TH), lds, st, a);
+        hipLaunchKernelGGL(coarse_middle_kernel, grid, dim3(CB_TH), 0, st, a);
+        hipLaunchKernelGGL((coarse_back_kernel<false, true>), halves, dim3(64), 0, st, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        continue;
       } else {
         hipLaunchKernelGGL((coarse_solve_kernel<COARSE_NQ, false, COARSE_THREADS>), grid, block, lds, st, a);
       }
