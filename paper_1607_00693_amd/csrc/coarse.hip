@@ -220,14 +220,18 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
     // coupling, column r - B) also goes to colB, the next pivot's column.
     // PG: the column above the diagonal, G[r - t][r], enters with the row
     // (and its entry at distance B goes to rowB, the next pivot's row).
+    // Rows enter in order; their node, window and right-hand side slots and
+    // element rows are counted along (with divisions by nix, WN and FN 2048
+    // samples of 8 x 8 took 91 us instead of 76).
+    int ix = 0, iy = 0, rw = 0, rf = 0, e0 = 0, e1 = 1 % 3;
     auto insert_row = [&](int r, double* colB, double* rowB) {
-      const int ix = r % nix, iy = r / nix, px = ix + 1, py = iy + 1;
+      const int px = ix + 1;
       if (ix == 0 && iy >= 1) {
         erow_store(iy + 2);
         erow_fetch(iy + 3);
       }
-      const double* eS = Ec + ((py - 1) % 3) * ncx * ES;
-      const double* eN = Ec + (py % 3) * ncx * ES;
+      const double* eS = Ec + e0 * ncx * ES;
+      const double* eN = Ec + e1 * ncx * ES;
       const double* sSW = eS + (px - 1) * ES;
       const double* sSE = eS + px * ES;
       const double* sNW = eN + (px - 1) * ES;
@@ -255,15 +259,24 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
           u += sget<PG>(sSW, 2, 0);
         }
         if (r - t >= 0) {
-          Wn[(r % WN) * WN + ((r - t) % WN)] = v;  // every entry of the row, once
-          if (PG && t > 0) Wn[((r - t) % WN) * WN + (r % WN)] = u;
+          const int cw = rw >= t ? rw - t : rw - t + WN;
+          Wn[rw * WN + cw] = v;  // every entry of the row, once
+          if (PG && t > 0) Wn[cw * WN + rw] = u;
           if (t == B && colB) colB[B - 1] = v;
           if (PG && t == B && rowB) rowB[B - 1] = u;
         }
       }
       if (tid == TH - 1) {
-        F[r % FN] = bnext;
+        F[rf] = bnext;
         bnext = node_load(r + 1);
+      }
+      rw = rw + 1 == WN ? 0 : rw + 1;
+      rf = rf + 1 == FN ? 0 : rf + 1;
+      if (++ix == nix) {
+        ix = 0;
+        ++iy;
+        e0 = e1;
+        e1 = e1 == 2 ? 0 : e1 + 1;
       }
     };
 
@@ -284,10 +297,10 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
     }
     __syncthreads();
 
+    int jj = 0, jf = 0;  // slots of row j
     for (int j = 0; j < nU; ++j) {
       const int b = j & 1;
       const double inv = pinv[b];
-      const int jj = j % WN;
       const int cnt = (j + B < nU - 1 ? j + B : nU - 1) - j;
       // rank-1 update of the trailing triangle, this lane's fixed entries:
       // all reads first, then all writes (distinct addresses), so that the
@@ -330,15 +343,17 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
       for (int t = 1 + tid; t <= cnt; t += TH) {
         const double l = colv[b][t - 1] * inv;
         Lc[(int64_t)j * WN + t] = PG ? rowv[b][t - 1] * inv : l;  // PG: (D^{-1} U)_{j, j+t}
-        F[(j + t) % FN] -= l * F[j % FN];
+        F[wrap(jf + t, FN)] -= l * F[jf];
       }
       if (tid == 0) {
         Lc[(int64_t)j * WN] = inv;
-        Us[j] = F[j % FN] * inv;  // z_j = y_j / d_j, overwritten by x_j below
+        Us[j] = F[jf] * inv;  // z_j = y_j / d_j, overwritten by x_j below
       }
       // the row entering the window takes the slot of row j (its last reader
       // was the phase before); its F slot is that of row j - 1
       if (j + 1 + B < nU) insert_row(j + 1 + B, colv[b ^ 1], PG ? rowv[b ^ 1] : nullptr);
+      jj = jj + 1 == WN ? 0 : jj + 1;
+      jf = jf + 1 == FN ? 0 : jf + 1;
       COARSE_SYNC();
     }
     if (tid == 0 && args.status) args.status[s] = bad ? STOMSFEM_ENOTSPD : STOMSFEM_OK;
@@ -1200,8 +1215,18 @@ static hipError_t launch_coarse_any(int ncx, int ncy, int64_t N, const double* S
       const dim3 grid((unsigned)n), block(TH);
       if (small) {
         if (pg) {
-          if (need <= 4)
+          // entries per lane as many as the B x B square needs: a pivot is a
+          // chain of dependent steps, and masked entries lengthen each (2048
+          // samples of 8 x 8, one entry instead of four: 107 -> 91 us; 32 of
+          // 20 x 20, seven instead of sixteen: 1.10 -> 0.82 ms)
+          if (need <= 1)
+            hipLaunchKernelGGL((coarse_solve_kernel<1, true, 64>), grid, block, lds, st, a);
+          else if (need <= 2)
+            hipLaunchKernelGGL((coarse_solve_kernel<2, true, 64>), grid, block, lds, st, a);
+          else if (need <= 4)
             hipLaunchKernelGGL((coarse_solve_kernel<4, true, 64>), grid, block, lds, st, a);
+          else if (need <= 7)
+            hipLaunchKernelGGL((coarse_solve_kernel<7, true, 64>), grid, block, lds, st, a);
           else
             hipLaunchKernelGGL((coarse_solve_kernel<16, true, 64>), grid, block, lds, st, a);
         } else {
