@@ -65,7 +65,7 @@ def profiled_traffic_per_pair():
     import hashlib
 
     prof = os.path.join(ROOT, "profiles", "upscale_mesh32_hbm_traffic.md")
-    src = os.path.join(ROOT, "paper_1607_00693_amd", "csrc", "upscale_tiled.hip")
+    src = os.path.join(ROOT, "paper_1607_00693_amd", "csrc", "upscale_rows.hip")
     try:
         vals = dict(line.split(": ", 1) for line in open(prof).read().splitlines() if ": " in line
                     and line.split(": ", 1)[0] in ("traffic_bytes_per_pair", "kernel_source_sha1"))
@@ -817,7 +817,7 @@ def measure_rb_os_sec52(log, nc=12, m=20, o=20, ntrain=64, N=1024):
     medium (16 bumps of radius 1/4 on a 4x4 grid, eps = 1/32; xi ~ U[-1,1]^16,
     training seed 2003, samples seed 1003): offline time (band-window
     snapshots, method of snapshots), both online stages against the
-    oversampled solve of the same pairs (register-tiled kernel)."""
+    oversampled solve of the same pairs (row-distributed kernel)."""
     import torch
 
     from paper_1607_00693_amd import stomsfem as sm

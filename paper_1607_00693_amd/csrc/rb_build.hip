@@ -514,7 +514,8 @@ __device__ __forceinline__ void rb_cholesky_band(double* L, const double* abar, 
 // latency of the reductions and of the rotation), order 13, modes 20.  With the
 // two-sided iteration, one rotation after the other in memory, the build of the
 // 64 patches took 20.5 ms, with its rounds in parallel in LDS 0.93 ms (13 sweeps);
-// now 0.52 ms.  A build end to end: n = 49 21.9 -> 1.23 ms, n = 121 190 -> 3.8 ms.
+// now 0.52 ms.  A build with the FP64 online stage, end to end: n = 49 21.9 -> 0.92 ms,
+// n = 121 190 -> 3.0 ms.
 template <int RT, bool DUAL>
 __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWork d) {
   extern __shared__ double smem[];
