@@ -43,7 +43,7 @@ constexpr int RB_LDS_N = 128;
 inline int rb_lda(int n) { return n <= RB_LDS_N ? n | 1 : n; }
 inline size_t rb_eigen_lds(bool dual, int m, int n, int rmax) {
   const size_t nI = (size_t)(m - 1) * (m - 1);
-  size_t d = 3 * (size_t)n + n;  // diagonal (two), values; pivots and order
+  size_t d = 4 * (size_t)n + 1 + n;  // diagonal (two), values, tails; pivots and order
   if (!dual) d += (n <= RB_LDS_N ? nI * (m + 1) : 0) + (size_t)rmax * nI;
   if (n <= RB_LDS_N) d += (size_t)n * rb_lda(n);
   return d * sizeof(double);
@@ -234,6 +234,17 @@ __device__ __forceinline__ double row_sum(double v) {
   return v + row_rotate<1>(v);
 }
 
+// largest value of the wavefront, the same in all lanes
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+  auto larger = [](unsigned a, unsigned b) { return a > b ? a : b; };
+  v = larger(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));
+  v = larger(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false));
+  v = larger(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false));
+  v = larger(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false));
+  return larger(larger(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                larger(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
 // 1 / sqrt(x) for normal x: one third-order step from the instruction's 2^-23
 __device__ __forceinline__ double inv_sqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
@@ -292,13 +303,9 @@ __device__ __forceinline__ int rb_pivoted_cholesky(double* A, int lda, int n, do
       const unsigned c = v > 0.0 ? ((unsigned)__double2hiint(v) & ~1023u) | (unsigned)i : 0u;
       key = c > key ? c : key;
     }
-#pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) {
-      const unsigned o = __shfl_xor(key, sft);
-      key = o > key ? o : key;
-    }
-    const int p = __builtin_amdgcn_readfirstlane(key & 1023u);
-    const double d = __builtin_amdgcn_readfirstlane(key) != 0 ? dk[p] : 0.0;
+    key = wave_max(key);
+    const int p = key & 1023u;
+    const double d = key != 0 ? dk[p] : 0.0;
     if (k == 0) {
       *d0 = d;
       floor = 1e-15 * d;
@@ -389,14 +396,16 @@ __device__ __forceinline__ void rb_jacobi(double* A, int lda, int n, int k, cons
           b = row_sum(b);
           c = row_sum(c);
           more = more || open(a, b, c);
-          double cs, sn;
-          schur_pair(a, b, c, &cs, &sn);
+          if (c * c > 1e-30 * a * b) {  // below, a rotation is rounding of the columns
+            double cs, sn;
+            schur_pair(a, b, c, &cs, &sn);
 #pragma unroll
-          for (int t = 0; t < RT; ++t) {
-            const int i = l + 16 * t;
-            if (i < n) {
-              P[i] = cs * x[t] - sn * y[t];
-              Q[i] = sn * x[t] + cs * y[t];
+            for (int t = 0; t < RT; ++t) {
+              const int i = l + 16 * t;
+              if (i < n) {
+                P[i] = cs * x[t] - sn * y[t];
+                Q[i] = sn * x[t] + cs * y[t];
+              }
             }
           }
         }
@@ -435,9 +444,9 @@ __device__ __forceinline__ void rb_jacobi(double* A, int lda, int n, int k, cons
 // lambda[0..nlam) (zeros beyond n), and the number of modes: r = min(rcap, rmax,
 // n, smallest r whose relative tail sqrt(sum_{q>r} lambda_q / sum lambda_q) <=
 // tail_tol, number of eigenvalues above RB_RANK_TOL lambda_max).  Whole
-// workgroup; r in thread 0.
-__device__ __forceinline__ int rb_sort_tail(const double* raw, int n, double* val, int* order, double tail_tol, int rcap,
-                                            int rmax, double* lambda, int nlam) {
+// workgroup.  tail: n + 1 values, first: one, of LDS.
+__device__ __forceinline__ int rb_sort_tail(const double* raw, int n, double* val, double* tail, int* order, int* first,
+                                            double tail_tol, int rcap, int rmax, double* lambda, int nlam) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const double x = raw[i];
     int rank = 0;
@@ -450,19 +459,22 @@ __device__ __forceinline__ int rb_sort_tail(const double* raw, int n, double* va
   }
   __syncthreads();
   for (int i = threadIdx.x; i < nlam; i += blockDim.x) lambda[i] = i < n ? val[i] : 0.0;
-  if (threadIdx.x != 0) return 0;
   double tot = 0.0;
-  for (int i = 0; i < n; ++i) tot += fmax(val[i], 0.0);
-  int r = n;
-  double tail = tot;
-  for (int q = 1; q <= n; ++q) {
-    tail -= fmax(val[q - 1], 0.0);
-    const double rel = tot > 0 ? sqrt(fmax(tail, 0.0) / tot) : 0.0;
-    if (rel <= tail_tol) {
-      r = q;
-      break;
-    }
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < n; ++i) tot += fmax(val[i], 0.0);
+    double t = tot;
+    for (int i = 0; i < n; ++i) tail[i] = t -= fmax(val[i], 0.0);
+    tail[n] = tot;
+    *first = n;
   }
+  __syncthreads();
+  tot = tail[n];
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const double rel = tot > 0 ? sqrt(fmax(tail[i], 0.0) / tot) : 0.0;
+    if (rel <= tail_tol) atomicMin(first, i + 1);
+  }
+  __syncthreads();
+  int r = *first;
   if (r > rcap) r = rcap;
   if (r > rmax) r = rmax;
   if (r > n) r = n;
@@ -509,13 +521,15 @@ __device__ __forceinline__ void rb_cholesky_band(double* L, const double* abar, 
 
 // One workgroup per patch, 16 lanes for each pair of columns.  RT: values of a
 // column per lane with the matrix in LDS, 0 with the matrix in memory.  At n = 49
-// (64 patches, ranks 15 to 49): factor of E 20 us, C 25, pivoted Cholesky 56,
-// Jacobi 64 to 310 (7 sweeps, 0.9 us a round: the columns through LDS and the
-// latency of the reductions and of the rotation), order 13, modes 20.  With the
-// two-sided iteration, one rotation after the other in memory, the build of the
-// 64 patches took 20.5 ms, with its rounds in parallel in LDS 0.93 ms (13 sweeps);
-// now 0.52 ms.  A build with the FP64 online stage, end to end: n = 49 21.9 -> 0.92 ms,
-// n = 121 190 -> 3.0 ms.
+// (64 patches, ranks 15 to 49) the phases took 20 us (factor of E), 25 (C), 56
+// (pivoted Cholesky), 64 to 310 (Jacobi: 7 sweeps, 0.9 us a round: the columns
+// through LDS and the latency of the reductions and of the rotation), 13 (order)
+// and 20 (modes), the kernel 515 us; with C formed in registers, the pivot's
+// maximum by DPP, the tails' roots in parallel and rotations below rounding
+// left out 466.  With the two-sided iteration, one rotation after the other in
+// memory, the build of the 64 patches took 20.5 ms, with its rounds in parallel
+// in LDS 0.93 ms (13 sweeps).  A build with the FP64 online stage, end to end:
+// n = 49 21.9 -> 0.85 ms, n = 121 190 -> 2.8 ms.
 template <int RT, bool DUAL>
 __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWork d) {
   extern __shared__ double smem[];
@@ -531,6 +545,7 @@ __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWor
   };
   double* diag = take(2 * n);
   double* val = take(n);
+  double* tail = take(n + 1);
   int* piv = (int*)take(n);  // pivots, then the order of the eigenvalues
   int* order = piv + n;
   double* L = DUAL ? nullptr : RT > 0 ? take(nI * LB) : d.L + (int64_t)K * nI * LB;
@@ -552,8 +567,9 @@ __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWor
   __syncthreads();
   if (!DUAL) {
     // C = L_E^T H L_E in place: H L_E by rows (a wavefront has read what it
-    // needs of its row before it writes), L_E^T (H L_E) by columns, and the
-    // upper part mirrored
+    // needs of its row before it writes), then the upper part of L_E^T (H L_E),
+    // formed in registers before any of it is written (in memory: by columns),
+    // and mirrored
     for (int i = tid / 64; i < n; i += nw)
       for (int j0 = 0; j0 < n; j0 += 64) {
         const int j = j0 + tid % 64;
@@ -565,15 +581,36 @@ __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWor
         __threadfence_block();
       }
     __syncthreads();
-    for (int j = tid; j < n; j += nt)
-      for (int i = 0; i <= j; ++i) {
-        double v = 0.0;
-        for (int k = i; k < n && k <= i + m; ++k) v += L[k * LB + k - i] * A[(int64_t)k * lda + j];
-        A[(int64_t)i * lda + j] = v;
+    if constexpr (RT > 0) {
+      constexpr int PER = 2 * RT;  // n^2 entries over 16 ceil(n / 2) threads or more
+      double v[PER];
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int i = (tid + e * nt) / n, j = (tid + e * nt) - i * n;
+        v[e] = 0.0;
+        if (i <= j && i < n)
+          for (int k = i; k < n && k <= i + m; ++k) v[e] += L[k * LB + k - i] * A[k * lda + j];
       }
-    __syncthreads();
-    for (int i = tid / 64; i < n; i += nw)
-      for (int j = i + 1 + tid % 64; j < n; j += 64) A[(int64_t)j * lda + i] = A[(int64_t)i * lda + j];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int i = (tid + e * nt) / n, j = (tid + e * nt) - i * n;
+        if (i <= j && i < n) {
+          A[i * lda + j] = v[e];
+          A[j * lda + i] = v[e];
+        }
+      }
+    } else {
+      for (int j = tid; j < n; j += nt)
+        for (int i = 0; i <= j; ++i) {
+          double v = 0.0;
+          for (int k = i; k < n && k <= i + m; ++k) v += L[k * LB + k - i] * A[(int64_t)k * lda + j];
+          A[(int64_t)i * lda + j] = v;
+        }
+      __syncthreads();
+      for (int i = tid / 64; i < n; i += nw)
+        for (int j = i + 1 + tid % 64; j < n; j += 64) A[(int64_t)j * lda + i] = A[(int64_t)i * lda + j];
+    }
     __syncthreads();
   }
   double d0;
@@ -591,13 +628,9 @@ __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWor
     if ((tid & 15) == 0) raw[c] = v;
   }
   __syncthreads();
-  const int rs = rb_sort_tail(raw, n, val, order, b.tail_tol, b.rcap, rmax, b.lambda + (int64_t)K * nI, nI);
-  if (tid == 0) {
-    rsel = rs;
-    b.rK[K] = rs;
-  }
-  __syncthreads();
-  const int r = rsel;
+  const int rs = rb_sort_tail(raw, n, val, tail, order, &rsel, b.tail_tol, b.rcap, rmax, b.lambda + (int64_t)K * nI, nI);
+  if (tid == 0) b.rK[K] = rs;
+  const int r = rs;
   double* Zk = b.Z + (int64_t)K * nI * rmax;
   if (DUAL) {
     for (int iq = tid; iq < nI * rmax; iq += nt) {
