@@ -29,13 +29,14 @@
 //                 per iteration 15.5 passes over a level-0 vector instead of
 //                 the 36.5 of one kernel per operation
 //   fmg_small    all levels of at most 32 elements per side, one workgroup per
-//                sample in LDS (a launch each for 70 sweeps and transfers took
-//                180 us per V-cycle)
+//                sample in LDS, 15.6 us (a launch each for 70 sweeps and
+//                transfers took 180); the thirty sweeps of at most 49 nodes by
+//                one wavefront with its stencil in registers
 //   scalars      the sums of the wavefronts' parts, in a fixed order
 // Samples that have converged are left alone.  16 samples of 1024 x 1024, 11
 // iterations: 19.3 -> 7.5 ms; per iteration fmg_down 233 us, fmg_up 149,
 // fmg_step 119 (3.8 to 4.5 TB/s counted without overlap; a copy reaches 5.1),
-// the levels below 146.  One sample of 128 x 128: 2.74 -> 0.78 ms.
+// the levels below 146.  One sample of 128 x 128: 2.74 -> 0.75 ms.
 //
 // Layout per level and sample: nodes (n+1) x (n+1), elements n x n; sample s
 // of a chunk at offset s (n+1)^2 (nodes) or s n^2 (elements).  Boundary nodes
@@ -160,14 +161,15 @@ __device__ __forceinline__ Elem elem(double a) {
   f.s = f.w + f.e;
   return f;
 }
-// weight / diagonal at a node between element rows f0 and f1 (zero where both are)
-__device__ __forceinline__ double damped_inverse(const Elem& f0, const Elem& f1) {
-  const double k = 4.0 * (f0.s + f1.s);
+// weight / k: two Newton steps take the instruction's estimate to full precision
+__device__ __forceinline__ double damped(double k) {
   double y = __builtin_amdgcn_rcp(k);
   y = fma(fma(-k, y, 1.0), y, y);
   y = fma(fma(-k, y, 1.0), y, y);
   return FMG_OMEGA * y;
 }
+// weight / diagonal at a node between element rows f0 and f1
+__device__ __forceinline__ double damped_inverse(const Elem& f0, const Elem& f1) { return damped(4.0 * (f0.s + f1.s)); }
 
 // A v row by row: row y of v, between element rows f0 = y - 1 and f1 = y, goes
 // to rows y - 1, y and y + 1; returns row y - 1 of A v, which is then complete.
@@ -487,7 +489,7 @@ __device__ __forceinline__ double small_apply(const SmallLevel& L, int ix, int i
   double v = kc * x[0];
   v -= ((aSW + aNW) * x[-1] + (aSE + aNE) * x[1] + (aSW + aSE) * x[-W] + (aNW + aNE) * x[W]) * (1.0 / 6.0);
   v -= (aSW * x[-W - 1] + aSE * x[-W + 1] + aNW * x[W - 1] + aNE * x[W + 1]) * (1.0 / 3.0);
-  *inv = FMG_OMEGA / kc;
+  *inv = damped(kc);
   return v;
 }
 
@@ -534,7 +536,7 @@ __global__ __launch_bounds__(FMG_SMALL_TB) void fmg_small_kernel(FmgLevel top, i
       const double* a = L.a + (iy - 1) * L.n + ix - 1;
       const double kc = (2.0 / 3.0) * ((a[0] + a[1]) + (a[L.n] + a[L.n + 1]));
       const int i = iy * (L.n + 1) + ix;
-      L.x[i] = FMG_OMEGA * L.b[i] / kc;
+      L.x[i] = damped(kc) * L.b[i];
     });
     __syncthreads();
   };
@@ -579,17 +581,25 @@ __global__ __launch_bounds__(FMG_SMALL_TB) void fmg_small_kernel(FmgLevel top, i
     start(L);
     if (L.n <= 8) {  // at most 49 nodes: one wavefront, without the workgroup's barriers
       if (tid < 64) {
-        const int m = L.n - 1, iy = 1 + tid / m, ix = 1 + tid % m, i = iy * (L.n + 1) + ix;
+        // a lane's node, its row of D^{-1} A and its right-hand side in registers
+        const int m = L.n - 1, W = L.n + 1;
         const bool on = tid < m * m;
+        const int iy = on ? 1 + tid / m : 1, ix = on ? 1 + tid % m : 1, at = iy * W + ix;
+        const double* a = L.a + (iy - 1) * L.n + ix - 1;
+        const double aSW = a[0], aSE = a[1], aNW = a[L.n], aNE = a[L.n + 1];
+        const double inv = damped((2.0 / 3.0) * ((aSW + aSE) + (aNW + aNE))), t = inv * (1.0 / 6.0), u = inv * (1.0 / 3.0);
+        const double wW = t * (aSW + aNW), wE = t * (aSE + aNE), wS = t * (aSW + aSE), wN = t * (aNW + aNE);
+        const double wSW = u * aSW, wSE = u * aSE, wNW = u * aNW, wNE = u * aNE, rhs = inv * L.b[at];
+        double* x = L.x + at;
+        double v = x[0];
         for (int k = 1; k < FMG_COARSE_SWEEPS; ++k) {
-          double v = 0.0;
-          if (on) {
-            double inv;
-            const double ax = small_apply(L, ix, iy, &inv);
-            v = L.x[i] + inv * (L.b[i] - ax);
-          }
+          // x + w D^{-1} (b - A x) with w D^{-1} A's diagonal w
+          double n = fma(wW, x[-1], fma(wE, x[1], rhs)), o = fma(wS, x[-W], wN * x[W]);
+          n = fma(wSW, x[-W - 1], fma(wSE, x[-W + 1], n));
+          o = fma(wNW, x[W - 1], fma(wNE, x[W + 1], o));
+          v = fma(1.0 - FMG_OMEGA, v, n + o);
           __threadfence_block();
-          if (on) L.x[i] = v;
+          if (on) x[0] = v;
           __threadfence_block();
         }
       }
