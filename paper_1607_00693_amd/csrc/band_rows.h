@@ -12,8 +12,9 @@
 // A DPP operand may be read two wait states after a vector instruction wrote
 // it.  The compiler does not look into inline assembly for that, so every
 // block below starts with its own s_nop 1 and writes no register that a
-// later instruction of the block reads through DPP.  All 64 lanes must be
-// active.
+// later instruction of the block reads: the accumulators of a block with more
+// than one instruction are early-clobber operands, so that an input of the
+// same value gets a register of its own.  All 64 lanes must be active.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -47,9 +48,9 @@ __device__ __forceinline__ void row_update(double* w, double col, double nl) {
             BR_DPP("%13", "%16", "%17", "%31")
             BR_DPP("%14", "%16", "%17", "%32")
             BR_DPP("%15", "%16", "%17", "%33")
-        : "+v"(w[C0]), "+v"(w[C0 + 1]), "+v"(w[C0 + 2]), "+v"(w[C0 + 3]), "+v"(w[C0 + 4]), "+v"(w[C0 + 5]),
-          "+v"(w[C0 + 6]), "+v"(w[C0 + 7]), "+v"(w[C0 + 8]), "+v"(w[C0 + 9]), "+v"(w[C0 + 10]), "+v"(w[C0 +
-          11]), "+v"(w[C0 + 12]), "+v"(w[C0 + 13]), "+v"(w[C0 + 14]), "+v"(w[C0 + 15])
+        : "+&v"(w[C0]), "+&v"(w[C0 + 1]), "+&v"(w[C0 + 2]), "+&v"(w[C0 + 3]), "+&v"(w[C0 + 4]), "+&v"(w[C0 + 5]),
+          "+&v"(w[C0 + 6]), "+&v"(w[C0 + 7]), "+&v"(w[C0 + 8]), "+&v"(w[C0 + 9]), "+&v"(w[C0 + 10]), "+&v"(w[C0 +
+          11]), "+&v"(w[C0 + 12]), "+&v"(w[C0 + 13]), "+&v"(w[C0 + 14]), "+&v"(w[C0 + 15])
         : "v"(col), "v"(nl), "n"(C0), "n"(C0 + 1), "n"(C0 + 2), "n"(C0 + 3), "n"(C0 + 4), "n"(C0 + 5), "n"(C0
           + 6), "n"(C0 + 7), "n"(C0 + 8), "n"(C0 + 9), "n"(C0 + 10), "n"(C0 + 11), "n"(C0 + 12), "n"(C0 + 13),
           "n"(C0 + 14), "n"(C0 + 15));
@@ -63,8 +64,8 @@ __device__ __forceinline__ void row_update(double* w, double col, double nl) {
             BR_DPP("%5", "%8", "%9", "%15")
             BR_DPP("%6", "%8", "%9", "%16")
             BR_DPP("%7", "%8", "%9", "%17")
-        : "+v"(w[C0]), "+v"(w[C0 + 1]), "+v"(w[C0 + 2]), "+v"(w[C0 + 3]), "+v"(w[C0 + 4]), "+v"(w[C0 + 5]),
-          "+v"(w[C0 + 6]), "+v"(w[C0 + 7])
+        : "+&v"(w[C0]), "+&v"(w[C0 + 1]), "+&v"(w[C0 + 2]), "+&v"(w[C0 + 3]), "+&v"(w[C0 + 4]), "+&v"(w[C0 + 5]),
+          "+&v"(w[C0 + 6]), "+&v"(w[C0 + 7])
         : "v"(col), "v"(nl), "n"(C0), "n"(C0 + 1), "n"(C0 + 2), "n"(C0 + 3), "n"(C0 + 4), "n"(C0 + 5), "n"(C0
           + 6), "n"(C0 + 7));
     if constexpr (N > 8) row_update<C0 + 8, N - 8>(w, col, nl);
@@ -74,7 +75,7 @@ __device__ __forceinline__ void row_update(double* w, double col, double nl) {
             BR_DPP("%1", "%4", "%5", "%7")
             BR_DPP("%2", "%4", "%5", "%8")
             BR_DPP("%3", "%4", "%5", "%9")
-        : "+v"(w[C0]), "+v"(w[C0 + 1]), "+v"(w[C0 + 2]), "+v"(w[C0 + 3])
+        : "+&v"(w[C0]), "+&v"(w[C0 + 1]), "+&v"(w[C0 + 2]), "+&v"(w[C0 + 3])
         : "v"(col), "v"(nl), "n"(C0), "n"(C0 + 1), "n"(C0 + 2), "n"(C0 + 3));
     if constexpr (N > 4) row_update<C0 + 4, N - 4>(w, col, nl);
   } else if constexpr (N == 3) {
@@ -82,13 +83,13 @@ __device__ __forceinline__ void row_update(double* w, double col, double nl) {
             BR_DPP("%0", "%3", "%4", "%5")
             BR_DPP("%1", "%3", "%4", "%6")
             BR_DPP("%2", "%3", "%4", "%7")
-        : "+v"(w[C0]), "+v"(w[C0 + 1]), "+v"(w[C0 + 2])
+        : "+&v"(w[C0]), "+&v"(w[C0 + 1]), "+&v"(w[C0 + 2])
         : "v"(col), "v"(nl), "n"(C0), "n"(C0 + 1), "n"(C0 + 2));
   } else if constexpr (N == 2) {
     asm("s_nop 1\n\t"
             BR_DPP("%0", "%2", "%3", "%4")
             BR_DPP("%1", "%2", "%3", "%5")
-        : "+v"(w[C0]), "+v"(w[C0 + 1])
+        : "+&v"(w[C0]), "+&v"(w[C0 + 1])
         : "v"(col), "v"(nl), "n"(C0), "n"(C0 + 1));
   } else if constexpr (N == 1) {
     asm("s_nop 1\n\t"
@@ -117,13 +118,13 @@ __device__ __forceinline__ double row_bcast(double v) {
 template <int L>
 __device__ __forceinline__ void row_rhs3(double* g, const double* f, double nl) {
   asm("s_nop 1\n\t" BR_DPP("%0", "%3", "%6", "%7") BR_DPP("%1", "%4", "%6", "%7") BR_DPP("%2", "%5", "%6", "%7")
-      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2])
+      : "+&v"(g[0]), "+&v"(g[1]), "+&v"(g[2])
       : "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(nl), "n"(L));
 }
 template <int L>
 __device__ __forceinline__ void row_rhs3_own(double* f, double nl) {
   asm("s_nop 1\n\t" BR_DPP("%0", "%0", "%3", "%4") BR_DPP("%1", "%1", "%3", "%4") BR_DPP("%2", "%2", "%3", "%4")
-      : "+v"(f[0]), "+v"(f[1]), "+v"(f[2])
+      : "+&v"(f[0]), "+&v"(f[1]), "+&v"(f[2])
       : "v"(nl), "n"(L));
 }
 
@@ -144,8 +145,8 @@ __device__ __forceinline__ void row_rhs10(double* g, const double* z, double c) 
           BR_DPP("%2", "%12", "%20", "%21") BR_DPP("%3", "%13", "%20", "%21") BR_DPP("%4", "%14", "%20", "%21")
               BR_DPP("%5", "%15", "%20", "%21") BR_DPP("%6", "%16", "%20", "%21") BR_DPP("%7", "%17", "%20", "%21")
                   BR_DPP("%8", "%18", "%20", "%21") BR_DPP("%9", "%19", "%20", "%21")
-      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7]), "+v"(g[8]),
-        "+v"(g[9])
+      : "+&v"(g[0]), "+&v"(g[1]), "+&v"(g[2]), "+&v"(g[3]), "+&v"(g[4]), "+&v"(g[5]), "+&v"(g[6]), "+&v"(g[7]), "+&v"(g[8]),
+        "+&v"(g[9])
       : "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "v"(z[4]), "v"(z[5]), "v"(z[6]), "v"(z[7]), "v"(z[8]), "v"(z[9]),
         "v"(c), "n"(L));
 }
@@ -153,7 +154,7 @@ __device__ __forceinline__ void row_rhs10(double* g, const double* z, double c) 
 // acc[i] += y(lane i of the row) * nl, i < 3
 __device__ __forceinline__ void row_lifts3(double* acc, double y, double nl) {
   asm("s_nop 1\n\t" BR_DPP("%0", "%3", "%4", "0") BR_DPP("%1", "%3", "%4", "1") BR_DPP("%2", "%3", "%4", "2")
-      : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2])
+      : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2])
       : "v"(y), "v"(nl));
 }
 
