@@ -361,9 +361,10 @@ int stomsfem_kl_blocks(int64_t npairs, int32_t m, int32_t Kuse, int32_t K, const
  * correction, thirty on the coarsest level; FP64 throughout), for every
  * sample until ||b - K u||_2 <= tol ||b||_2 or max_iter iterations.  iters
  * device int32 [nsamples] or NULL: the iterations each sample took; status
- * device [nsamples] or NULL: OK or ENOCONV.  Samples in chunks of at most
- * 64 (about 65 MB each at nfine = 1024, in the library workspace).  Reads a
- * counter back every four iterations, so it synchronises `stream`.
+ * device [nsamples] or NULL: OK or ENOCONV.  A sample's u and iterations
+ * are the same bits in whatever batch it is solved.  Samples in chunks of at
+ * most 64 (about 65 MB each at nfine = 1024, in the library workspace).  Reads
+ * a counter back every four iterations, so it synchronises `stream`.
  *
  * stomsfem_two_level_mc: per interior coarse node i of the nc x nc mesh,
  * mean[i] = M[U_H][i] + M[u_h - U_Hh][i] over the two sample sets (U_H device

@@ -52,6 +52,8 @@ constexpr double FMG_OMEGA = 0.8;    // Jacobi weight
 constexpr int FMG_COARSE_SWEEPS = 30;
 constexpr int FMG_SMALL = 32;        // largest level of fmg_small
 constexpr int FMG_ROWS = 8;          // shortest segment of a stream
+constexpr int FMG_SUM = 4;           // rows to a part of a sum
+constexpr int FMG_SUMS = 128;        // most parts of a segment
 
 struct FmgLevel {
   int n;            // elements per side
@@ -80,25 +82,33 @@ struct Stream {
   int n, W, lane, ix;
   unsigned cx;
   int64_t s;
-  int part, y0, y1;
+  int wave, strip, y0, y1;
   bool inner, own;
 };
 struct StreamGrid {
   int strips, segs, rows;
+  int parts;  // of a sum over a sample's rows
 };
 
-// Strips of 64 - 2 H columns; segments so that about 5120 wavefronts (five per
-// SIMD, what the registers of fmg_down allow) are in flight, with at least 16
-// rows to the 2 H or so that are computed twice.
-inline StreamGrid stream_grid(int n, int64_t N, int H, int waves) {
+// Strips of 64 - 2 H columns; segments of at least FMG_ROWS rows, so that about
+// `waves` wavefronts are in flight: 4096 for fmg_down and fmg_up (four per SIMD,
+// what their registers allow), 5120 for fmg_step.  How many samples share a
+// batch decides the segments, so a sum goes by strip and block of FMG_SUM rows:
+// a sample's sums, and with them its solution, are the same bits in any batch.
+// Segments of whole blocks where there is a sum (whole blocks of 8 rows left
+// fmg_up 7% fewer wavefronts at 1024 and 16 samples, 135 -> 146 us; of 4, as
+// many), else of an even count (a coarse row belongs to its fine row's segment).
+inline StreamGrid stream_grid(int n, int64_t N, int H, int waves, bool sums = true) {
   StreamGrid g;
   g.strips = (n + 63 - 2 * H) / (64 - 2 * H);
   int64_t segs = waves / (g.strips * N);
   const int64_t most = (n + FMG_ROWS - 1) / FMG_ROWS;
-  segs = segs < 1 ? 1 : segs > most ? most : segs;
-  g.rows = (int)((n + segs - 1) / segs);
-  g.rows += g.rows & 1;  // a coarse row belongs to the segment of its fine row
+  const int64_t least = (n + FMG_SUM * FMG_SUMS - 1) / (FMG_SUM * FMG_SUMS);
+  segs = segs < least ? least : segs > most ? most : segs;
+  const int unit = sums ? FMG_SUM : 2;
+  g.rows = (int)((n + segs - 1) / segs + unit - 1) / unit * unit;
   g.segs = (n + g.rows - 1) / g.rows;
+  g.parts = g.strips * ((n + FMG_SUM - 1) / FMG_SUM);
   return g;
 }
 
@@ -107,17 +117,19 @@ template <int H>
 __device__ __forceinline__ bool stream_of(Stream& t, const StreamGrid& g, int n, int64_t N, const int32_t* active) {
   // (all of it the same in the 64 lanes: row addresses stay in scalar registers)
   auto uniform = [](unsigned v) { return (int)__builtin_amdgcn_readfirstlane(v); };
-  const unsigned id = blockIdx.x * (FMG_TB / 64) + uniform(threadIdx.x >> 6), per = g.strips * g.segs;
+  t.wave = uniform(threadIdx.x >> 6);
+  const unsigned id = blockIdx.x * (FMG_TB / 64) + t.wave, per = g.strips * g.segs;
   if (id >= per * (unsigned)N) return false;
   const int s = uniform(id / per);
   t.s = s;
   if (active && !active[s]) return false;
-  t.part = uniform(id - s * per);
-  const int seg = uniform((unsigned)t.part / (unsigned)g.strips), strip = uniform(t.part - seg * g.strips);
+  const int in_s = uniform(id - s * per);
+  const int seg = uniform((unsigned)in_s / (unsigned)g.strips);
+  t.strip = uniform(in_s - seg * g.strips);
   t.n = n;
   t.W = n + 1;
   t.lane = threadIdx.x & 63;
-  t.ix = strip * (64 - 2 * H) + t.lane - H;
+  t.ix = t.strip * (64 - 2 * H) + t.lane - H;
   t.cx = t.ix < 0 ? 0 : t.ix > n ? n : t.ix;
   t.inner = t.ix > 0 && t.ix < n;
   t.own = t.inner && t.lane >= H && t.lane < 64 - H;
@@ -133,6 +145,14 @@ __device__ __forceinline__ double get(const double* row, unsigned bytes) {
 }
 __device__ __forceinline__ void put(double* row, unsigned bytes, double v) {
   *reinterpret_cast<double*>(reinterpret_cast<char*>(row) + bytes) = v;
+}
+
+// An offset that the compiler cannot add to an array's address ahead of the loop,
+// at two registers each: fmg_up would spill, and a reload waits for every load
+// that is on its way (153 us with its sums in LDS, 135 so).
+__device__ __forceinline__ unsigned fresh(unsigned bytes) {
+  asm("" : "+v"(bytes));
+  return bytes;
 }
 
 // value of the lane to the left / to the right (zero past the wavefront)
@@ -186,10 +206,56 @@ struct Apply {
   }
 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int s = 1; s < 64; s <<= 1) v += __shfl_xor(v, s);
-  return v;
+// sum over the wavefront, the same in all lanes: within the DPP rows of 16 by
+// rotations, then the four rows' sums
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  union { double d; int w[2]; } x{v}, y;
+  y.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], 0x120 + N, 0xf, 0xf, false);
+  y.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], 0x120 + N, 0xf, 0xf, false);
+  return y.d;
 }
+__device__ __forceinline__ double lane_of(double v, int lane) {
+  union { double d; int w[2]; } x{v}, y;
+  y.w[0] = __builtin_amdgcn_readlane(x.w[0], lane);
+  y.w[1] = __builtin_amdgcn_readlane(x.w[1], lane);
+  return y.d;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
+  return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
+// The sum of a stream's rows by blocks of FMG_SUM, kept in LDS until the segment
+// is done (a store to memory in the loop would count among the loads that are on
+// their way and shorten them).  OFF: how far the first row of the loop lies
+// before y0, AHEAD: rows per turn.
+template <int OFF, int AHEAD>
+struct BlockSum {
+  double* sums;  // FMG_SUMS of LDS
+  double acc = 0.0;
+  // after row y has been added, in place k of its turn (one place of a turn can
+  // end a block)
+  __device__ __forceinline__ void row(const Stream& t, int y, int k) {
+    if (k != (FMG_SUM - 1 + OFF) % AHEAD || (y & (FMG_SUM - 1)) != FMG_SUM - 1 || y < t.y0 || y >= t.y1) return;
+    acc = wave_sum(acc);
+    if (t.lane == 0) sums[(y - t.y0) / FMG_SUM] = acc;
+    acc = 0.0;
+  }
+  __device__ __forceinline__ void store(const Stream& t, const StreamGrid& g, double* part) {
+    const int blocks = (t.y1 - t.y0 + FMG_SUM - 1) / FMG_SUM;
+    if (t.y1 & (FMG_SUM - 1)) {
+      acc = wave_sum(acc);
+      if (t.lane == 0) sums[blocks - 1] = acc;
+    }
+    __threadfence_block();
+    for (int i = t.lane; i < blocks; i += 64)
+      part[t.s * g.parts + (int64_t)(t.y0 / FMG_SUM + i) * g.strips + t.strip] = sums[i];
+  }
+};
 
 // Two Jacobi sweeps from zero on the right-hand side b, the residual and its
 // restriction.
@@ -243,7 +309,8 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_down_kernel(DownArgs d) {
   double b1 = 0.0, b2 = 0.0;             // b, one and two rows behind its newest
   double x1 = 0.0, i1 = 0.0;             // first sweep and weight / diagonal, one row behind
   double h1 = 0.0, h2r = 0.0;            // rows of the residual, restricted in x
-  double acc = 0.0;
+  __shared__ double sums[SRC == 1 ? FMG_TB / 64 : 1][SRC == 1 ? FMG_SUMS : 1];
+  BlockSum<(PRE ? 3 : 0) + 2 * LAG, AHEAD> sum{sums[SRC == 1 ? t.wave : 0]};
   auto load_u = [&](int y) { return get(u + (int64_t)(y < 1 ? 0 : y < n ? y - 1 : n - 2) * (n - 1), cu); };
   double ra[AHEAD], rv[AHEAD], rr[AHEAD], ru[AHEAD];
   auto fetch = [&](int k, int y) {
@@ -278,8 +345,9 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_down_kernel(DownArgs d) {
       if (mine) {
         put(d.r1 + node + (int64_t)yb * W, cb, b);
         put(u + (int64_t)(yb - 1) * (n - 1), cu, d.first ? al * p1 : fma(al, p1, vu));
-        acc = fma(b, b, acc);
+        sum.acc = fma(b, b, sum.acc);
       }
+      sum.row(t, yb, k);
       p1 = v;
     } else if (SRC == 2) {
       b = t.inner && row_in(yb) ? h2 : 0.0;
@@ -311,10 +379,7 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_down_kernel(DownArgs d) {
       i1 = inv;
     }
   }
-  if (SRC == 1) {
-    acc = wave_sum(acc);
-    if (t.lane == 0) d.part[t.s * (d.g.strips * d.g.segs) + t.part] = acc;
-  }
+  if (SRC == 1) sum.store(t, d.g, d.part);
 }
 
 // x = t + P x_c, two Jacobi sweeps on it; DOT: the part of b.x.
@@ -336,20 +401,20 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_up_kernel(UpArgsMg d) {
   const double* a = d.L.a + t.s * n * n;
   const unsigned cb = 8 * t.cx, ca = 8 * (t.cx < (unsigned)n ? t.cx : n - 1);
   const double *tv = d.L.t + node, *bv = d.L.b + node;
-  const unsigned c0 = t.cx >> 1, c1 = c0 < (unsigned)nc ? c0 + 1 : nc;
+  const unsigned c0 = t.cx < (unsigned)n ? t.cx >> 1 : nc - 1, cc = 8 * c0;
   const double* xc = d.xc + t.s * Wc * Wc;
   const bool elem_in = t.ix >= 0 && t.ix < n, odd = t.ix & 1;
   auto row_in = [&](int y) { return y > 0 && y < n; };
   // raw values of a row (of the nearest one outside the domain); masked when used,
   // not where they are loaded, which would wait for them
-  auto load_a = [&](int y) { return get(a + (int64_t)(y < 0 ? 0 : y < n ? y : n - 1) * n, ca); };
-  auto load_v = [&](const double* q, int y) { return get(q + (int64_t)(y < 0 ? 0 : y < n ? y : n) * W, cb); };
+  auto load_a = [&](int y) { return get(a + (int64_t)(y < 0 ? 0 : y < n ? y : n - 1) * n, fresh(ca)); };
+  auto load_v = [&](const double* q, int y) { return get(q + (int64_t)(y < 0 ? 0 : y < n ? y : n) * W, fresh(cb)); };
   auto mask_a = [&](double v, int y) { return elem_in && y >= 0 && y < n ? v : 0.0; };
   auto mask_v = [&](double v, int y) { return t.inner && row_in(y) ? v : 0.0; };
   auto coarse_row = [&](int yc) { return xc + (int64_t)(yc < 0 ? 0 : yc < nc ? yc : nc) * Wc; };
   auto coarse = [&](double l, double r, int yc) {  // x_c interpolated in x, coarse row yc
     const bool in = yc > 0 && yc < nc;
-    const double lv = in && c0 > 0 && c0 < (unsigned)nc ? l : 0.0, rv = in && c1 < (unsigned)nc ? r : 0.0;
+    const double lv = in && c0 > 0 ? l : 0.0, rv = in && c0 + 1 < (unsigned)nc ? r : 0.0;
     return odd ? 0.5 * (lv + rv) : lv;
   };
   const int first = t.y0 - 2, last = t.y1 - 1 + 2;
@@ -357,28 +422,31 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_up_kernel(UpArgsMg d) {
   Apply a1, a2;
   double v1 = 0.0, w1 = 0.0;              // before and after the first sweep, one row behind
   double b1 = 0.0, b2 = 0.0, i1 = 0.0, i2 = 0.0;
-  double low = coarse(get(coarse_row(first >> 1), 8 * c0), get(coarse_row(first >> 1), 8 * c1), first >> 1);
-  double acc = 0.0;
-  double ra[AHEAD], rt[AHEAD], rb[AHEAD], rl[AHEAD / 2], rh[AHEAD / 2];
+  double low = coarse(get(coarse_row(first >> 1), cc), get(coarse_row(first >> 1), cc + 8), first >> 1);
+  __shared__ double sums[DOT ? FMG_TB / 64 : 1][DOT ? FMG_SUMS : 1];
+  BlockSum<4, AHEAD> sum{sums[DOT ? t.wave : 0]};
+  double ra[AHEAD], rt[AHEAD], rb[AHEAD], rl, rh;
   auto fetch = [&](int k, int y) {
     ra[k] = load_a(y);
     rt[k] = load_v(tv, y);
     rb[k] = load_v(bv, y);
-    if (k & 1) {  // first is even
-      const double* q = coarse_row((y + 1) >> 1);
-      rl[k / 2] = get(q, 8 * c0);
-      rh[k / 2] = get(q, 8 * c1);
-    }
+  };
+  auto fetch_coarse = [&](int y) {  // for the odd row y: the coarse row above it, one pair of rows ahead
+    const double* q = coarse_row((y + 1) >> 1);
+    rl = get(q, fresh(cc));
+    rh = get(q, fresh(cc) + 8);
   };
 #pragma unroll
   for (int k = 0; k < AHEAD; ++k) fetch(k, first + k);
+  fetch_coarse(first + 1);  // first is even
   for (int y8 = first; y8 <= last; y8 += AHEAD)
 #pragma unroll
   for (int k = 0; k < AHEAD; ++k) {
     const int y = y8 + k;
     const double va = ra[k], vt = rt[k], b = mask_v(rb[k], y);
-    const double ul = rl[k / 2], uh = rh[k / 2];
+    const double ul = rl, uh = rh;
     fetch(k, y + AHEAD);
+    if (k & 1) fetch_coarse(y + 2);
     __builtin_amdgcn_sched_barrier(0);
     f2 = f1;
     f1 = f0;
@@ -396,9 +464,10 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_up_kernel(UpArgsMg d) {
     const double aw = a2.push(w, f2, f1);                                        // row y - 2
     if (t.own && y - 2 >= t.y0 && y - 2 < t.y1 && row_in(y - 2)) {
       const double z = fma(i2, b2 - aw, w1);
-      put(d.L.x + node + (int64_t)(y - 2) * W, cb, z);
-      if (DOT) acc = fma(b2, z, acc);
+      put(d.L.x + node + (int64_t)(y - 2) * W, fresh(cb), z);
+      if (DOT) sum.acc = fma(b2, z, sum.acc);
     }
+    if (DOT) sum.row(t, y - 2, k);
     w1 = w;
     v1 = v;
     b2 = b1;
@@ -406,10 +475,7 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_up_kernel(UpArgsMg d) {
     i2 = i1;
     i1 = inv;
   }
-  if (DOT) {
-    acc = wave_sum(acc);
-    if (t.lane == 0) d.part[t.s * (d.g.strips * d.g.segs) + t.part] = acc;
-  }
+  if (DOT) sum.store(t, d.g, d.part);
 }
 
 // p1 = z + beta p0 (first: p1 = z) and the part of p1.A p1
@@ -443,7 +509,9 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_step_kernel(StepArgs d) {
   const int first = t.y0 - 1, last = t.y1;
   Elem f0 = elem(mask_a(load_a(first - 1), first - 1)), f1{};
   Apply ap;
-  double p1 = 0.0, acc = 0.0;
+  __shared__ double sums[FMG_TB / 64][FMG_SUMS];
+  BlockSum<2, AHEAD> sum{sums[t.wave]};
+  double p1 = 0.0;
   double ra[AHEAD], rz[AHEAD], rp[AHEAD];
   auto fetch = [&](int k, int y) {
     ra[k] = load_a(y);
@@ -463,12 +531,12 @@ __global__ __launch_bounds__(FMG_TB, 4) void fmg_step_kernel(StepArgs d) {
     f0 = elem(mask_a(va, y));
     const double p = mask_v(fma(be, p0, z), y);
     const double q = ap.push(p, f1, f0);  // row y - 1
-    if (t.own && y - 1 >= t.y0 && y - 1 < t.y1) acc = fma(p1, q, acc);
+    if (t.own && y - 1 >= t.y0 && y - 1 < t.y1) sum.acc = fma(p1, q, sum.acc);
+    sum.row(t, y - 1, k);
     if (t.own && y >= t.y0 && y < t.y1 && row_in(y)) put(d.p1 + node + (int64_t)y * W, cb, p);
     p1 = p;
   }
-  acc = wave_sum(acc);
-  if (t.lane == 0) d.part[t.s * (d.g.strips * d.g.segs) + t.part] = acc;
+  sum.store(t, d.g, d.part);
 }
 
 // ---- small levels ----
@@ -710,6 +778,7 @@ __global__ __launch_bounds__(FMG_TB) void fmg_scalar_kernel(FmgCg c, int parts, 
   __shared__ double red[FMG_TB / 64];
   double v = 0.0;
   if (STEP > 0) {
+#pragma unroll 8
     for (int k = threadIdx.x; k < parts; k += FMG_TB) v += c.part[s * parts + k];
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -780,7 +849,7 @@ hipError_t fmg_vcycle(FmgLevel* lv, int nlev, int l, int64_t N, const int32_t* a
     if (l > 0) {
       DownArgs d{};
       d.L = L;
-      d.g = stream_grid(L.n, N, 4, 4096);
+      d.g = stream_grid(L.n, N, 4, 4096, false);
       d.N = N;
       d.active = active;
       d.bc = lv[l + 1].b;
@@ -791,13 +860,13 @@ hipError_t fmg_vcycle(FmgLevel* lv, int nlev, int l, int64_t N, const int32_t* a
     if (e != hipSuccess) return e;
     UpArgsMg u{};
     u.L = L;
-    u.g = stream_grid(L.n, N, 2, 4096);
+    u.g = stream_grid(L.n, N, 2, 4096, l == 0);
     u.N = N;
     u.active = active;
     u.xc = lv[l + 1].x;
     u.part = part;
     if (l == 0) {
-      *parts = u.g.strips * u.g.segs;
+      *parts = u.g.parts;
       hipLaunchKernelGGL(fmg_up_kernel<true>, dim3(stream_blocks(u.g, N)), dim3(FMG_TB), 0, st, u);
     } else {
       hipLaunchKernelGGL(fmg_up_kernel<false>, dim3(stream_blocks(u.g, N)), dim3(FMG_TB), 0, st, u);
@@ -814,9 +883,9 @@ hipError_t fmg_vcycle(FmgLevel* lv, int nlev, int l, int64_t N, const int32_t* a
   return e;
 }
 
-// most parts per sample of any sum: strips of 56 columns, the shortest segments
+// most parts per sample of any sum: strips of 56 columns
 int64_t fmg_parts(int n) {
-  const int64_t streams = (int64_t)((n + 55) / 56) * ((n + FMG_ROWS - 1) / FMG_ROWS);
+  const int64_t streams = (int64_t)((n + 55) / 56) * ((n + FMG_SUM - 1) / FMG_SUM);
   return streams > 256 ? streams : 256;
 }
 
@@ -923,7 +992,7 @@ hipError_t launch_fine_pcg(const double* a, int n, int64_t N, double tol, int ma
     sa.p1 = p[1 - (it & 1)];
     sa.first = it == 0;
     hipLaunchKernelGGL(fmg_step_kernel, dim3(stream_blocks(sa.g, N)), b, 0, st, sa);
-    hipLaunchKernelGGL(fmg_scalar_kernel<2>, gs, bs, 0, st, c, sa.g.strips * sa.g.segs, it);
+    hipLaunchKernelGGL(fmg_scalar_kernel<2>, gs, bs, 0, st, c, sa.g.parts, it);
     d.L = lv[0];
     d.p = sa.p1;
     d.r0 = r[it & 1];
@@ -936,7 +1005,7 @@ hipError_t launch_fine_pcg(const double* a, int n, int64_t N, double tol, int ma
     lv[0].b = d.r1;
     const bool check = (it % 4 == 3) || it == max_iter - 1;
     if (check) hipLaunchKernelGGL(fmg_zero_kernel, dim3(1), dim3(1), 0, st, c.nactive);
-    hipLaunchKernelGGL(fmg_scalar_kernel<3>, gs, bs, 0, st, c, d.g.strips * d.g.segs, it);
+    hipLaunchKernelGGL(fmg_scalar_kernel<3>, gs, bs, 0, st, c, d.g.parts, it);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (check) {
