@@ -638,6 +638,7 @@ int stomsfem_upscale_surrogate(stomsfem_model* model, const double* xi, int32_t 
  * Algorithm 2).  status device [nsamples][M] or NULL: 0 = interpolated,
  * 1 = computed plainly, STOMSFEM_ENOTSPD from such a solve.  *nfallback
  * (host, may be NULL) receives the number of plainly computed pairs.
+ * A pair's S is the same bits in whatever batch it is computed.
  * Synchronises `stream` once (to read that number); may grow a model-owned
  * buffer (a synchronous allocation) when nsamples exceeds earlier calls.
  * ------------------------------------------------------------------------ */
@@ -745,7 +746,8 @@ int stomsfem_sgi_apply(stomsfem_model* model, const double* xi, int32_t nxi, int
  * from kappa device [nsamples][ncy m][ncx m] (FP64).  status device
  * [nsamples][M] or NULL: 0 = interpolated, 1 = computed plainly, ENOTSPD from
  * such a solve; *nfallback (host, may be NULL) = the number of plainly
- * computed pairs.  Synchronises `stream` once; may grow a model-owned buffer.
+ * computed pairs.  A pair's S is the same bits in whatever batch it is
+ * computed.  Synchronises `stream` once; may grow a model-owned buffer.
  *
  * stomsfem_kl_interp_os_build (offline): the same for the oversampled
  * Petrov-Galerkin stiffness (Sec. 2.2) in the parameters of the oversampled

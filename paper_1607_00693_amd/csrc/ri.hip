@@ -136,7 +136,7 @@ __device__ __forceinline__ void inner_sum(const table_t* T, double w, const doub
 #pragma unroll
       for (int e = 0; e < NE; ++e) acc[e] = fma(wd, T[d * NE + e], acc[e]);
     }
-  } else {
+  } else if constexpr (NN < 4) {
 #pragma unroll
     for (int d2 = 0; d2 < NN; ++d2) {
       const double w2 = w * c2[d2];
@@ -145,6 +145,25 @@ __device__ __forceinline__ void inner_sum(const table_t* T, double w, const doub
         const double wd = w2 * c3[d3];
 #pragma unroll
         for (int e = 0; e < NE; ++e) acc[e] = fma(wd, T[(d2 * NN + d3) * NE + e], acc[e]);
+      }
+    }
+  } else {
+    // the table values in batches that the scalar registers hold, each waited for
+    // once: left to itself the compiler waits for most loads one by one here
+    // (8192 samples at 5 nodes 145 us so, 221 without)
+    constexpr int D = 40 / NE;
+#pragma unroll
+    for (int i0 = 0; i0 < NN * NN; i0 += D) {
+      double v[D * NE];
+#pragma unroll
+      for (int i = 0; i < D * NE; ++i)
+        if (i0 + i / NE < NN * NN) v[i] = T[i0 * NE + i];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = i0; i < i0 + D && i < NN * NN; ++i) {
+        const double wd = w * c2[i / NN] * c3[i % NN];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) acc[e] = fma(wd, v[(i - i0) * NE + e], acc[e]);
       }
     }
   }
@@ -176,11 +195,21 @@ __device__ __forceinline__ void inner_sum2(const table_t* T, double w, const dou
     inner_sum<NN, 2, NE>(T, w, c2, c3, acc);
 }
 
-// The share of part `part` of `PARTS`: every PARTS-th value of the slower
-// variables (with fewer than three variables part 0 takes all).
+// The sum over the slower variables goes in four runs of rows, each from zero
+// and added in order, also where one wavefront takes them all (from four nodes
+// on: tables that launch_apply_nn never shares have one run).  A pair's value is
+// then the same bits however many wavefronts share its table.
+constexpr int RI_RUNS = 4;
+template <int NN>
+constexpr int ri_runs() { return NN >= 4 ? RI_RUNS : 1; }
+
+// Run `part` of the sum (PARTS = RI_RUNS; with fewer than three variables run 0
+// is all of it) or the whole of it (PARTS = 1: this thread's entries of `done`,
+// 256 apart in LDS, hold the runs before; in registers they would cost a
+// wavefront per SIMD from seven nodes on).
 template <int NN, int KV, int NE, int PARTS>
 __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_KMAX], double lo,
-                                        double hi, double (&acc)[NE], int part) {
+                                        double hi, double (&acc)[NE], int part, double* done) {
   if (KV < 3 && part > 0) return;
   double c0[NN], c1[NN], c2[NN], c3[NN];
   // variables are consumed from the fastest: the last one pairs with c3
@@ -194,25 +223,45 @@ __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_K
     inner_sum2<NN, NE>(T, 1.0, c2, c3, acc);
   } else if constexpr (KV < 2) {
     inner_sum<NN, K2, NE>(T, 1.0, c2, c3, acc);
-  } else if constexpr (KV == 3) {
-#pragma unroll 1
-    for (int d1 = 0; d1 < NN; ++d1) {
-      if (d1 % PARTS == part) inner_sum2<NN, NE>(T + (int64_t)d1 * inner * NE, c1[0], c2, c3, acc);
-      shift_down<NN>(c1);
-    }
   } else {
-#pragma unroll 1
-    for (int d0 = 0; d0 < NN; ++d0) {
-      double c1r[NN];
+    constexpr int rows = KV == 3 ? NN : NN * NN, runs = ri_runs<NN>();
+    static_assert(PARTS == 1 || PARTS == runs, "parts are runs");
+    auto row = [&](int i, double w) {
+      if constexpr (PARTS == 1 && runs > 1) {
+        if (i == rows / 4 || i == rows * 2 / 4 || i == rows * 3 / 4) {
 #pragma unroll
-      for (int q = 0; q < NN; ++q) c1r[q] = c1[q];
+          for (int e = 0; e < NE; ++e) {
+            done[256 * e] = i == rows / 4 ? acc[e] : done[256 * e] + acc[e];
+            acc[e] = 0.0;
+          }
+        }
+      }
+      if (PARTS == 1 || (i >= rows * part / PARTS && i < rows * (part + 1) / PARTS))
+        inner_sum2<NN, NE>(T + (int64_t)i * inner * NE, w, c2, c3, acc);
+    };
+    if constexpr (KV == 3) {
 #pragma unroll 1
       for (int d1 = 0; d1 < NN; ++d1) {
-        if ((d0 * NN + d1) % PARTS == part)
-          inner_sum2<NN, NE>(T + (int64_t)(d0 * NN + d1) * inner * NE, c0[0] * c1r[0], c2, c3, acc);
-        shift_down<NN>(c1r);
+        row(d1, c1[0]);
+        shift_down<NN>(c1);
       }
-      shift_down<NN>(c0);
+    } else {
+#pragma unroll 1
+      for (int d0 = 0; d0 < NN; ++d0) {
+        double c1r[NN];
+#pragma unroll
+        for (int q = 0; q < NN; ++q) c1r[q] = c1[q];
+#pragma unroll 1
+        for (int d1 = 0; d1 < NN; ++d1) {
+          row(d0 * NN + d1, c0[0] * c1r[0]);
+          shift_down<NN>(c1r);
+        }
+        shift_down<NN>(c0);
+      }
+    }
+    if constexpr (PARTS == 1 && runs > 1) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) acc[e] = done[256 * e] + acc[e];
     }
   }
 }
@@ -220,8 +269,8 @@ __device__ __forceinline__ void ri_eval(const table_t* T, const double (&x)[RI_K
 // Grid: ceil(nsamples PARTS / 256) x npatch workgroups in one dimension,
 // remapped so that all workgroups of one patch run on the same XCD (workgroups
 // are dealt to the 8 XCDs round-robin), which keeps each table in one L2.  With
-// PARTS = 4 the four wavefronts of a workgroup share the table rows of the same
-// 64 samples and their sums are added in LDS.
+// PARTS = 4 the four wavefronts of a workgroup take the runs of the same 64
+// samples and their sums are added in LDS.
 template <int NN, int NE, int PARTS>
 __global__ __launch_bounds__(256) void ri_apply_kernel(RiApplyArgs a, int64_t nblk_s, int64_t nwork) {
   const int64_t b = blockIdx.x;
@@ -250,15 +299,17 @@ __global__ __launch_bounds__(256) void ri_apply_kernel(RiApplyArgs a, int64_t nb
   }
   if (PARTS == 1 && !inside) return;
   const table_t* T = (const table_t*)(a.table + a.off[K] * NE);
+  __shared__ double runs[PARTS == 1 && ri_runs<NN>() > 1 ? NE : 1][256];
+  double* done = &runs[0][threadIdx.x];
   double acc[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) acc[e] = 0.0;
   switch (k) {
-    case 0: ri_eval<NN, 0, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
-    case 1: ri_eval<NN, 1, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
-    case 2: ri_eval<NN, 2, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
-    case 3: ri_eval<NN, 3, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
-    default: ri_eval<NN, 4, NE, PARTS>(T, x, a.lo, a.hi, acc, part); break;
+    case 0: ri_eval<NN, 0, NE, PARTS>(T, x, a.lo, a.hi, acc, part, done); break;
+    case 1: ri_eval<NN, 1, NE, PARTS>(T, x, a.lo, a.hi, acc, part, done); break;
+    case 2: ri_eval<NN, 2, NE, PARTS>(T, x, a.lo, a.hi, acc, part, done); break;
+    case 3: ri_eval<NN, 3, NE, PARTS>(T, x, a.lo, a.hi, acc, part, done); break;
+    default: ri_eval<NN, 4, NE, PARTS>(T, x, a.lo, a.hi, acc, part, done); break;
   }
   if constexpr (PARTS > 1) {
     __shared__ double sums[PARTS - 1][NE][PER];
@@ -318,15 +369,15 @@ static hipError_t launch_apply_parts(const RiApplyArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Up to two wavefronts of pairs per SIMD (one at five nodes or fewer, where the
-// unrolled rows of the single wavefront hide more) the table's scalar loads are
-// waited for: four wavefronts to a table row then.  One wavefront per SIMD: 7
-// nodes 247 -> 97 us, 5 nodes 60 -> 43; two: 221 -> 178 and 5 nodes 62 us alone;
-// four: 351 alone against 372, 5 nodes 103 against 125.
+// Up to two wavefronts of pairs per SIMD the table's scalar loads are waited for:
+// four wavefronts to a table then, the same bits as one.  With a table's 64
+// patches: 1000 samples at 7 nodes 247 us alone, 97 shared; 2048 samples at 5
+// nodes 77 alone, 66 shared; 2100 samples alone (4 nodes 55 us, 5 nodes 79, 7
+// nodes 200), where four wavefronts of sharing would already fill the SIMDs.
 template <int NN>
 static hipError_t launch_apply_nn(const RiApplyArgs& a, hipStream_t st) {
-  if constexpr (NN >= 4)
-    if ((a.nsamples + 63) / 64 * a.npatch <= (NN > 5 ? 2048 : 1024)) return launch_apply_parts<NN, 4>(a, st);
+  if constexpr (ri_runs<NN>() > 1)
+    if ((a.nsamples + 63) / 64 * a.npatch <= 2048) return launch_apply_parts<NN, RI_RUNS>(a, st);
   return launch_apply_parts<NN, 1>(a, st);
 }
 
