@@ -369,8 +369,8 @@ __global__ __launch_bounds__(TH) void coarse_solve_kernel(CoarseArgs args) {
 // both ends at once: one workgroup takes the first rows, one the last, as the
 // first rows of the domain turned by 180 degrees, and between B + 2 and B + 9
 // rows remain for coarse_middle_kernel.  256 samples of 64 x 64: 1.82 -> 1.06 ms,
-// the backward pass 0.53 -> 0.33.  Meshes of fewer than B + 18 rows take the
-// pivot-per-barrier kernel.
+// the backward pass 0.53 -> 0.33.  Flat meshes, where the middle takes longer
+// than the rows saved, go from one end (SPLIT = false).
 //   wavefront 0 applies the rank-CB_NB update of panel P-1 to the columns of
 //      panel P, then factors panel P: every lane factors the CB_NB x CB_NB
 //      diagonal block (broadcast LDS reads, no cross-lane traffic) and
@@ -416,7 +416,13 @@ __host__ __device__ inline CoarseSplit coarse_split(int B, int nU) {
   p.mid = nU - p.top - p.bottom;
   return p;
 }
-__host__ __device__ inline bool coarse_splits(int B, int nU) { return nU >= B + 2 + 2 * CB_NB; }
+// Whether the split pays (by the mesh alone: a sample's U is the same bits in any
+// batch).  One, 256 and 4096 samples from one end / split, us: 33 x 3 (64 rows) 49 /
+// 66, 53 / 78, 333 / 542; 33 x 5 (128) 84 / 87, 89 / 103, 601 / 807; 48 x 4 (141) 99
+// / 98, 105 / 116, 731 / 951; 64 x 4 (189) 128 / 121, 136 / 143, 1123 / 1330; 40 x 5
+// (156; from one end with one workgroup per CU) 106 / 94, 114 / 112, 1320 / 952.
+__host__ __device__ inline bool coarse_splits(int B, int nU) { return 2 * nU >= 3 * B + 190; }
+static_assert(3 * CB_BMAX + 190 >= 2 * (CB_BMAX + 2 + 2 * CB_NB), "a split leaves at least a panel to each end");
 
 // Packed entry q of an element matrix after a turn by 180 degrees (local nodes
 // 0 and 2, 1 and 3 change places).
@@ -425,6 +431,7 @@ __device__ __forceinline__ int turned_entry(int q) {
   return (int)((T >> (4 * q)) & 15);
 }
 
+template <bool SPLIT>
 __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs args) {
   constexpr int NB = CB_NB;
   extern __shared__ double smem[];
@@ -445,12 +452,12 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t s = blockIdx.x >> 1;
-  const int half = blockIdx.x & 1;  // 1: the domain turned by 180 degrees
+  const int64_t s = SPLIT ? blockIdx.x >> 1 : blockIdx.x;
+  const int half = SPLIT ? blockIdx.x & 1 : 0;  // 1: the domain turned by 180 degrees
   if (s >= args.nsamples) return;
   const CoarseSplit split = coarse_split(B, nU);
-  const int np = half ? split.bottom : split.top;  // pivots
-  const int nr = np + B;                           // rows of the half
+  const int np = !SPLIT ? nU : half ? split.bottom : split.top;  // pivots
+  const int nr = SPLIT ? np + B : nU;                            // rows of the half, or all
   const double* Ss = args.S + s * (int64_t)ncx * ncy * 10;
   double* Us = args.U + s * (int64_t)nU;
   double* Ls = args.work + s * ((int64_t)nU * BW + 1);
@@ -597,15 +604,17 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
       }
       // the diagonal block (rows and columns j0 .. j0 + NB - 1) and the rhs
       // of its rows in every lane: lanes 0 .. NB-1 hold the block rows, the
-      // other lanes read them back (same addresses: broadcast)
+      // other lanes read them back (same addresses: broadcast); rows past the
+      // last one (halves are whole panels) are an identity block so that no
+      // pivot is zero there
 #pragma unroll
       for (int k = 0; k < NB; ++k) *(lane < NB && k <= lane ? &Bk[lane][k] : jk) = x1[k];
       double blk[NB][NB], fb[NB];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
 #pragma unroll
-        for (int k = 0; k <= i; ++k) blk[i][k] = Bk[i][k];
-        fb[i] = F[wrapn(sj + i)];
+        for (int k = 0; k <= i; ++k) blk[i][k] = SPLIT || j0 + i < np ? Bk[i][k] : i == k ? 1.0 : 0.0;
+        fb[i] = SPLIT || j0 + i < np ? F[wrapn(sj + i)] : 0.0;
       }
       // every lane factors the block (right-looking, pivot order) and
       // carries its own two rows along: entry (R, j0 + k) receives the
@@ -620,7 +629,7 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
         inv = fma(fma(-d, inv, 1.0), inv, inv);
         inv = fma(fma(-d, inv, 1.0), inv, inv);
         dinv[pp] = inv;
-        if (!(d > 0.0)) bad = 1;
+        if ((SPLIT || j0 + pp < np) && !(d > 0.0)) bad = 1;
         const double y = fb[pp];
         yv[pp] = y;
 #pragma unroll
@@ -722,16 +731,18 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
       if (P >= 1) {
         // columns j0 - NB .. j0 - 1 of L (a contiguous block of the
         // workspace) and their z
-        const int jp = j0 - NB;
+        const int jp = j0 - NB, ncol = SPLIT || np - jp > NB ? NB : np - jp;
         double* Lb = Lc + (int64_t)jp * BW;
 #pragma unroll
-        for (int pp = 0; pp < NB; ++pp)
+        for (int pp = 0; pp < NB; ++pp) {
+          if (!SPLIT && pp >= ncol) break;
           for (int t = lane; t < BW; t += 64) {
             const double* src =
                 t == 0 ? &dq[pb][pp] : (t < NB - pp ? &Lq[pb][pp][pp + t] : &Lp[pb][pp][t - (NB - pp)]);
             Lb[pp * BW + t] = *src;
           }
-        if (lane < NB) Us[half ? nU - 1 - (jp + lane) : jp + lane] = zq[pb][lane];
+        }
+        if (lane < ncol) Us[half ? nU - 1 - (jp + lane) : jp + lane] = zq[pb][lane];
       }
       // panel P-1's row slots: cleared, then the nonzeros of the rows first
       // touched by panel P+1 (LDS operations of one wavefront complete in
@@ -751,6 +762,10 @@ __global__ __launch_bounds__(CB_TH, 2) void coarse_blocked_kernel(CoarseArgs arg
     }
     sj = wrapn(sj + NB);
     COARSE_SYNC();
+  }
+  if constexpr (!SPLIT) {
+    if (tid == 0 && args.status) args.status[s] = bad ? STOMSFEM_ENOTSPD : STOMSFEM_OK;
+    return;
   }
   // what the half adds to the matrix and right-hand side of the middle's B rows
   // next to it; the last panel's update of its first NB columns is still to come
@@ -1274,15 +1289,23 @@ static hipError_t launch_coarse_any(int ncx, int ncy, int64_t N, const double* S
         }
       } else if (pg) {
         hipLaunchKernelGGL((coarse_solve_kernel<4, true, COARSE_THREADS>), grid, block, lds, st, a);
-      } else if (use_blocked(ncx, pg) && coarse_splits(ncx, nU)) {
+      } else if (use_blocked(ncx, pg)) {
         // the kernel's dynamic-LDS limit raised before each launch (a host call;
         // it then holds on whichever device is current)
-        const hipError_t attr = hipFuncSetAttribute((const void*)coarse_blocked_kernel,
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)coarse_blocked_lds_bytes(CB_BMAX));
+        const bool splits = coarse_splits(ncx, nU);
+        const hipError_t attr = hipFuncSetAttribute(
+            splits ? (const void*)coarse_blocked_kernel<true> : (const void*)coarse_blocked_kernel<false>,
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)coarse_blocked_lds_bytes(CB_BMAX));
         if (attr != hipSuccess) return attr;
+        if (!splits) {
+          hipLaunchKernelGGL(coarse_blocked_kernel<false>, grid, dim3(CB_TH), lds, st, a);
+          hipLaunchKernelGGL(coarse_back_kernel<false>, grid, dim3(64), 0, st, a);
+          hipError_t e = hipGetLastError();
+          if (e != hipSuccess) return e;
+          continue;
+        }
         const dim3 halves((unsigned)(2 * n));
-        hipLaunchKernelGGL(coarse_blocked_kernel, halves, dim3(CB_TH), lds, st, a);
+        hipLaunchKernelGGL(coarse_blocked_kernel<true>, halves, dim3(CB_TH), lds, st, a);
         hipLaunchKernelGGL(coarse_middle_kernel, grid, dim3(CB_TH), 0, st, a);
         hipLaunchKernelGGL((coarse_back_kernel<false, true>), halves, dim3(64), 0, st, a);
         hipError_t e = hipGetLastError();
