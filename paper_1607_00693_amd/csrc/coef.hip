@@ -8,6 +8,7 @@
 // centre cell lies within ceil(rho*g) cells of the point are visited, in
 // increasing j.
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 
@@ -26,10 +27,10 @@ struct CoefArgs {
 // thread keeps those of its element in registers (sqrt psi_j of the bumps that
 // reach the tile at all, up to COEF_KEEP of them) and a sample costs two
 // operations per bump, an exponential and the store; the samples' xi_j of the
-// kept bumps are shared in LDS.  Tiles that more bumps reach evaluate the sum
-// per element and sample, and so do small batches (the direct kernel), where
-// the table would not pay.  The oscillating factor is separable, so its sines
-// are evaluated once per tile row and column.
+// kept bumps are shared in LDS.  Tiles that more bumps reach and batches too small
+// for the table take the direct kernel, the sum per element and sample; a tile
+// whose xi are not finite does so here.  The oscillating factor is separable, so
+// its sines are evaluated once per tile row and column.
 //
 // Bound by the exponential (about 30 vector instructions) and the stores (3.9
 // TB/s): 1024 samples of 1024 x 1024 elements 8.4 -> 2.2 ms, 16 384 samples of
@@ -51,8 +52,10 @@ __device__ __forceinline__ void coef_samples(const double (*xs)[COEF_KEEP], cons
   }
 }
 
-// Direct form: one sample per workgroup, the bump sum per element.
-template <typename T>
+// Direct form: one sample per workgroup, the bump sum per element.  NEAR: discs
+// that reach one cell at most (a kernel of its own, as the unrolled sum takes the
+// registers of a wavefront per SIMD).
+template <typename T, bool NEAR>
 __global__ __launch_bounds__(256) void coef_bumps_direct_kernel(CoefArgs c, int tiles_x) {
   __shared__ double sx[COEF_TILE], sy[COEF_TILE];
   const int64_t tiles = (int64_t)tiles_x * tiles_x;
@@ -60,7 +63,6 @@ __global__ __launch_bounds__(256) void coef_bumps_direct_kernel(CoefArgs c, int 
   const double h = 1.0 / c.nfine;
   const int lane = threadIdx.x;
   const BumpParams bp{c.g, c.rho, c.eps, c.base, c.amp, c.beta};
-  const bool near = c.rho * c.g <= 1.0;
   // workgroup-uniform loop over (sample, tile): the grid is capped so that
   // the launch stays within the per-dispatch thread limit
   for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
@@ -76,10 +78,19 @@ __global__ __launch_bounds__(256) void coef_bumps_direct_kernel(CoefArgs c, int 
     const int ix = tx * COEF_TILE + (lane % COEF_TILE), iy = ty * COEF_TILE + lane / COEF_TILE;
     const double x = (ix + 0.5) * h, y = (iy + 0.5) * h;
     const double* xi = c.xi + s * c.nxi;
+    // a tile in one bump cell has the same candidates for every element: the
+    // loop's bounds and the xi loads are then uniform
+    const int x1 = min(tx * COEF_TILE + COEF_TILE - 1, c.nfine - 1), y1 = min(ty * COEF_TILE + COEF_TILE - 1, c.nfine - 1);
+    const int cx = bump_cell((tx * COEF_TILE + 0.5) * h, c.g), cy = bump_cell((ty * COEF_TILE + 0.5) * h, c.g);
+    const bool one_cell = cx == bump_cell((x1 + 0.5) * h, c.g) && cy == bump_cell((y1 + 0.5) * h, c.g);
     double e = 0.0;
-    if (ix < c.nfine && iy < c.nfine)
-      e = exp(c.beta * (near ? bump_field_near(x, y, xi, bp, bump_cell(x, c.g), bump_cell(y, c.g))
-                             : bump_field(x, y, xi, bp)));
+    if (ix < c.nfine && iy < c.nfine) {
+      if (one_cell)
+        e = bump_field_cell(x, y, xi, bp, cx, cy);
+      else
+        e = NEAR ? bump_field_near(x, y, xi, bp, bump_cell(x, c.g), bump_cell(y, c.g)) : bump_field(x, y, xi, bp);
+      e = exp(c.beta * e);
+    }
     __syncthreads();
     if (ix < c.nfine && iy < c.nfine)
       ((T*)c.a)[(s * c.nfine + iy) * (int64_t)c.nfine + ix] =
@@ -185,6 +196,33 @@ __global__ __launch_bounds__(256) void coef_bumps_kernel(CoefArgs c, int tiles_x
   }
 }
 
+// Most bumps whose discs reach a tile, or more than COEF_KEEP: by the smallest
+// distances of the tiles' element centres to the bumps' centres along one axis
+// (an upper bound, as the smallest ones need not meet in one tile).
+static int coef_reaching(int nfine, int g, double rho) {
+  double gap[COEF_KEEP], near[COEF_KEEP];
+  int n = 0;
+  const int tiles = (nfine + COEF_TILE - 1) / COEF_TILE;
+  for (int t = 0; t < tiles; ++t) {
+    const double x0 = (t * COEF_TILE + 0.5) / nfine, x1 = (std::min(t * COEF_TILE + COEF_TILE, nfine) - 0.5) / nfine;
+    const double lo = std::max(0.0, std::floor((x0 - rho) * g - 0.5)), hi = std::min(g - 1.0, std::ceil((x1 + rho) * g - 0.5));
+    int m = 0;
+    for (double j = lo; j <= hi; ++j) {
+      const double c = (j + 0.5) / g, d = std::max({0.0, x0 - c, c - x1});
+      if (!(d < rho * (1.0 + 1e-12))) continue;
+      if (m == COEF_KEEP) return COEF_KEEP + 1;
+      near[m++] = d;
+    }
+    std::sort(near, near + m);
+    for (int k = 0; k < m; ++k) gap[k] = k < n ? std::min(gap[k], near[k]) : near[k];
+    n = std::max(n, m);
+  }
+  int count = 0;
+  for (int i = 0; i < n; ++i)
+    for (int k = 0; k < n; ++k) count += gap[i] * gap[i] + gap[k] * gap[k] < rho * rho * (1.0 + 1e-12);
+  return count;
+}
+
 hipError_t launch_coef_bumps(int64_t nsamples, int nfine, const double* xi, int nxi, int g, double rho, double eps,
                              double base, double amp, double beta, void* a, int a_dtype, hipStream_t st) {
   CoefArgs c{nsamples, nfine, nxi, g, rho, eps, base, amp, beta, xi, a};
@@ -192,19 +230,35 @@ hipError_t launch_coef_bumps(int64_t nsamples, int nfine, const double* xi, int 
   const int64_t tiles = (int64_t)tiles_x * tiles_x;
   // enough workgroups to fill the GPU several times over first, then up to
   // COEF_PER samples each to share a tile's table
-  const int64_t per = std::max<int64_t>(1, std::min<int64_t>(COEF_PER, nsamples * tiles / 8192));
+  int64_t per = std::max<int64_t>(1, std::min<int64_t>(COEF_PER, nsamples * tiles / 8192));
+  // The table costs a search over the candidates and a barrier for each, so it
+  // pays from a number of samples on that grows with the bumps it holds: per
+  // element and sample / with the table, us: 64 x 64 elements, 4 x 4 bumps, 9 to a
+  // tile, 3000 samples (5 to a group) 132 / 147, 4096 (8) 180 / 133; 256 x 256,
+  // 200 samples (6), 4 to a tile 129 / 100, 16 to a tile 143 / 195; discs of two
+  // cells, 16 to a tile, 3000 samples of 64 x 64 (5) 178 / 210, 12 of 1024 x 1024
+  // (6) 151 / 138.  Where more than COEF_KEEP reach a tile it never does (64
+  // samples of 1024 x 1024, 64 to a tile, 1.55 / 2.36 ms).
+  if (per > 1) {
+    const int reach = coef_reaching(nfine, g, rho);
+    if (reach > COEF_KEEP || per < (rho * g > 1.0 ? 6 : 3 + reach / 2)) per = 1;
+  }
   const int64_t groups = (nsamples + per - 1) / per;
   int64_t blocks = groups * tiles;
   if (blocks == 0) return hipSuccess;
   if (blocks > (1 << 20)) blocks = 1 << 20;
-  if (per == 1 && a_dtype == STOMSFEM_F32)
-    hipLaunchKernelGGL(coef_bumps_direct_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, c, tiles_x);
-  else if (per == 1)
-    hipLaunchKernelGGL(coef_bumps_direct_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, st, c, tiles_x);
-  else if (a_dtype == STOMSFEM_F32)
-    hipLaunchKernelGGL(coef_bumps_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, c, tiles_x, (int)per, groups);
-  else
-    hipLaunchKernelGGL(coef_bumps_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, st, c, tiles_x, (int)per, groups);
+  const dim3 grid((unsigned)blocks), block(256);
+  const bool f32 = a_dtype == STOMSFEM_F32;
+  if (per > 1) {
+    if (f32) hipLaunchKernelGGL(coef_bumps_kernel<float>, grid, block, 0, st, c, tiles_x, (int)per, groups);
+    else hipLaunchKernelGGL(coef_bumps_kernel<double>, grid, block, 0, st, c, tiles_x, (int)per, groups);
+  } else if (rho * g <= 1.0) {
+    if (f32) hipLaunchKernelGGL((coef_bumps_direct_kernel<float, true>), grid, block, 0, st, c, tiles_x);
+    else hipLaunchKernelGGL((coef_bumps_direct_kernel<double, true>), grid, block, 0, st, c, tiles_x);
+  } else {
+    if (f32) hipLaunchKernelGGL((coef_bumps_direct_kernel<float, false>), grid, block, 0, st, c, tiles_x);
+    else hipLaunchKernelGGL((coef_bumps_direct_kernel<double, false>), grid, block, 0, st, c, tiles_x);
+  }
   return hipGetLastError();
 }
 

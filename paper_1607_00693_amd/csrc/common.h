@@ -97,15 +97,23 @@ struct BumpParams {
   double rho, eps, base, amp, beta;
 };
 
-// sqrt psi_j at (x, y) of the bump centred in cell (jx, jy): 1 - |x - c_j|^2 /
-// rho^2, or 0 outside the disc.  Every kernel that forms the family's
-// coefficient takes it, the sum (in increasing j, terms fma(xi_j q, q, sum))
-// and the oscillating factor in these roundings, so that a coefficient
-// regenerated for one element is the generated field's bit for bit.
-__device__ __forceinline__ double bump_root(double x, double y, int jx, int jy, double ginv, double rinv2) {
+// Every kernel that forms the family's coefficient takes a bump's squared
+// distance r2 = |x - c_j|^2 / rho^2 (sqrt psi_j = 1 - r2 inside the disc), the
+// sum (in increasing j, terms fma(xi_j q, q, sum)) and the oscillating factor in
+// these roundings, so that a coefficient regenerated for one element is the
+// generated field's bit for bit.
+__device__ __forceinline__ double bump_offset(double x, double centre, double ginv) {
+  return __builtin_fma(-ginv, centre, x);  // centre: of cell j, j + 0.5
+}
+__device__ __forceinline__ double bump_r2(double dx, double dy2, double rinv2) {
 #pragma clang fp contract(off)
-  const double dx = __builtin_fma(-ginv, jx + 0.5, x), dy = __builtin_fma(-ginv, jy + 0.5, y);
-  const double r2 = __builtin_fma(dx, dx, dy * dy) * rinv2;
+  return __builtin_fma(dx, dx, dy2) * rinv2;
+}
+__device__ __forceinline__ double bump_square(double dy) { return dy * dy; }
+// sqrt psi_j at (x, y) of the bump centred in cell (jx, jy), 0 outside the disc
+__device__ __forceinline__ double bump_root(double x, double y, int jx, int jy, double ginv, double rinv2) {
+  const double dx = bump_offset(x, jx + 0.5, ginv), dy = bump_offset(y, jy + 0.5, ginv);
+  const double r2 = bump_r2(dx, bump_square(dy), rinv2);
   return r2 < 1.0 ? 1.0 - r2 : 0.0;
 }
 __device__ __forceinline__ double bump_osc(const BumpParams& bp, double sx, double sy) {
@@ -121,18 +129,22 @@ __device__ __forceinline__ double bump_osc(const BumpParams& bp, double sx, doub
 // The same sum for a point whose centre cell (bx, by) the caller supplies
 // (a workgroup whose points share one cell passes it as a uniform value, so
 // the loop bounds and the xi loads are uniform too).
-// XS: stride between consecutive xi_j in memory (1 for a sample's row of xi).
-template <int XS = 1>
 __device__ __forceinline__ double bump_field_cell(double x, double y, const double* xs, const BumpParams& bp, int bx,
                                                   int by) {
   const double ginv = 1.0 / bp.g, rinv2 = 1.0 / (bp.rho * bp.rho);
   const int reach = (int)ceil(bp.rho * bp.g);
+  const int x0 = max(bx - reach, 0), x1 = min(bx + reach, bp.g - 1);
   double field = 0.0;
-  for (int jy = max(by - reach, 0); jy <= min(by + reach, bp.g - 1); ++jy)
-    for (int jx = max(bx - reach, 0); jx <= min(bx + reach, bp.g - 1); ++jx) {
-      const double q = bump_root(x, y, jx, jy, ginv, rinv2);
-      if (q > 0.0) field = __builtin_fma(xs[(jy * bp.g + jx) * XS] * q, q, field);
+  for (int jy = max(by - reach, 0); jy <= min(by + reach, bp.g - 1); ++jy) {
+    const double dy2 = bump_square(bump_offset(y, jy + 0.5, ginv));
+    for (int jx = x0; jx <= x1; ++jx) {
+      const double r2 = bump_r2(bump_offset(x, jx + 0.5, ginv), dy2, rinv2);
+      if (r2 < 1.0) {
+        const double q = 1.0 - r2;
+        field = __builtin_fma(xs[jy * bp.g + jx] * q, q, field);
+      }
     }
+  }
   return field;
 }
 
@@ -159,9 +171,8 @@ __device__ __forceinline__ double bump_field_near(double x, double y, const doub
 // centre cell of a point along one axis
 __device__ __forceinline__ int bump_cell(double x, int g) { return min((int)(x * g), g - 1); }
 
-template <int XS = 1>
 __device__ __forceinline__ double bump_field(double x, double y, const double* xs, const BumpParams& bp) {
-  return bump_field_cell<XS>(x, y, xs, bp, bump_cell(x, bp.g), bump_cell(y, bp.g));
+  return bump_field_cell(x, y, xs, bp, bump_cell(x, bp.g), bump_cell(y, bp.g));
 }
 
 // Conductivity of feature j of the channels-and-inclusions medium:
