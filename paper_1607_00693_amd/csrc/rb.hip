@@ -397,17 +397,27 @@ __device__ __forceinline__ bool rb_small_solve(const T* v, int r, double S3[3][3
   return ok;
 }
 
-// FP64 reference online stage: one thread per pair, the 64 samples of a
+// FP64 reference online stage: one thread per pair.  SAMPLES: the 64 samples of a
 // wavefront on one patch, so that the table is read at uniform addresses
 // (scalar loads): 65 536 pairs at m = 8 took 260 us with the lanes along the
-// patches, 66 gathers per coefficient; 55 us so.
+// patches, 66 gathers per coefficient; 55 us so.  Few samples leave most of those
+// lanes idle; on many patches they go along the patches.  Both do the same
+// operations, hence the same bits.
 typedef __attribute__((address_space(4))) const double rb_table_t;
-template <int RMAX, typename TA>
+template <int RMAX, typename TA, bool SAMPLES>
 __global__ __launch_bounds__(64) void rb_apply_f64_kernel(RbApplyArgs ra, int64_t nsamples, unsigned groups) {
   const UpArgs& args = ra.up;
   const int m = args.m, Mc = args.ncx * args.ncy;
-  const int K = (int)(blockIdx.x / groups);
-  const int64_t s = (int64_t)(blockIdx.x % groups) * 64 + threadIdx.x;
+  int64_t s = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  int K;
+  if constexpr (SAMPLES) {
+    K = (int)(blockIdx.x / groups);
+    s = (int64_t)(blockIdx.x % groups) * 64 + threadIdx.x;
+  } else {
+    const int64_t i = s;
+    s = i / Mc;
+    K = (int)(i - s * Mc);
+  }
   if (s >= nsamples) return;
   const int64_t p = s * Mc + K;
   const TA* a = (const TA*)args.a + block_offset(s, K, args.ncx, args.ncy, m);
@@ -416,12 +426,30 @@ __global__ __launch_bounds__(64) void rb_apply_f64_kernel(RbApplyArgs ra, int64_
   double v[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) v[q] = 0.0;
-  const rb_table_t* G = (const rb_table_t*)(ra.G64 + (int64_t)K * ra.KD * ra.PP);
+  using Table = std::conditional_t<SAMPLES, const rb_table_t*, const double*>;
+  Table G = (Table)(ra.G64 + (int64_t)K * ra.KD * ra.PP);
   for (int ey = 0; ey < m; ++ey)
     for (int ex = 0; ex < m; ++ex, G += ra.PP) {
       const double ae = ld(a, ey * lda + ex);
+      if constexpr (SAMPLES) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) v[q] += ae * G[q];
+        for (int q = 0; q < P; ++q) v[q] += ae * G[q];
+      } else {
+        // each lane has cache lines of its own: a batch of loads takes what a line
+        // holds before other wavefronts drive it out (8 samples of 96 x 96 patches
+        // 487 us with loads and sums mixed, 362 so)
+        constexpr int BATCH = 8;
+#pragma unroll
+        for (int q0 = 0; q0 < P; q0 += BATCH) {
+          double t[BATCH];
+#pragma unroll
+          for (int q = q0; q < q0 + BATCH && q < P; ++q) t[q - q0] = G[q];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = q0; q < q0 + BATCH && q < P; ++q) v[q] += ae * t[q - q0];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   double S3[3][3];
   const bool ok = rb_small_solve<RMAX, double>(v, ra.rK[K], S3);
@@ -653,11 +681,21 @@ hipError_t launch_rb_apply(const RbApplyArgs& ra, int a_dtype, bool f64, hipStre
   if (ra.rmax != 8) return hipErrorInvalidValue;
   if (f64) {
     const int64_t Mc = (int64_t)u.ncx * u.ncy, n = u.npairs / Mc, groups = (n + 63) / 64;
-    const dim3 g((unsigned)(groups * Mc));
-    if (a_dtype == STOMSFEM_F32)
-      hipLaunchKernelGGL((rb_apply_f64_kernel<8, float>), g, dim3(64), 0, st, ra, n, (unsigned)groups);
+    // 1 and 8 samples along the samples / the patches, us: 96 x 96 patches at m = 8
+    // 447 / 259, 452 / 361; 128 x 128 at m = 4 149 / 55, 151 / 126; 200 x 200 at m = 4
+    // 447 / 104, 459 / 605; 64 x 64 at m = 8 179 / 171, 180 / 188; 32 x 32 63 / 170
+    const bool patches = n <= 8 && Mc > 4096;
+    const dim3 g((unsigned)(patches ? (u.npairs + 63) / 64 : groups * Mc)), block(64);
+    const unsigned gr = (unsigned)groups;
+    const bool f32 = a_dtype == STOMSFEM_F32;
+    if (patches && f32)
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, float, false>), g, block, 0, st, ra, n, gr);
+    else if (patches)
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, double, false>), g, block, 0, st, ra, n, gr);
+    else if (f32)
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, float, true>), g, block, 0, st, ra, n, gr);
     else
-      hipLaunchKernelGGL((rb_apply_f64_kernel<8, double>), g, dim3(64), 0, st, ra, n, (unsigned)groups);
+      hipLaunchKernelGGL((rb_apply_f64_kernel<8, double, true>), g, block, 0, st, ra, n, gr);
     return hipGetLastError();
   }
   if (ra.PP != 80 || ra.KD % RBA_KC != 0 || ra.KD < u.m * u.m) return hipErrorInvalidValue;
