@@ -61,9 +61,9 @@ __global__ __launch_bounds__(64) void cell_phi_kernel(PhiArgs pa) {
   int io[PHI_Q], ko[PHI_Q], fi[PHI_F], fl[PHI_F];
 #pragma unroll
   for (int k = 0; k < PHI_Q; ++k) {
-    const int q = tid + 64 * k;
-    int i = 0;
-    while ((i + 1) * (i + 2) / 2 <= q) ++i;
+    // row i of entry q: 8 q + 1 runs from (2 i + 1)^2 to 8 below (2 i + 3)^2; one
+    // more leaves the root's rounding no say
+    const int q = tid + 64 * k, i = (int)((sqrtf((float)(8 * q + 2)) - 1.0f) * 0.5f);
     io[k] = i;
     ko[k] = q - i * (i + 1) / 2;
   }

@@ -26,6 +26,9 @@ constexpr int RB_NMAX = 1024;       // largest eigenproblem (primal nI or dual 3
 constexpr int RB_EIGEN = 1024;      // most threads of the eigen kernel
 constexpr double RB_RANK_TOL = 1e-12;
 constexpr size_t RB_LDS = 160 * 1024 - 512;  // less the static variables
+constexpr int RB_MANY = 256;        // patches that fill the GPU with a workgroup each
+constexpr int RB_TABLE_BLOCKS = 8192;
+constexpr int RB_TINY = 4;          // unknowns of the patches with their own Gram kernel
 
 // Buffers of a build.  The eigenproblem has n = nI (primal) or ns (dual)
 // unknowns.
@@ -57,9 +60,10 @@ int64_t rb_work_layout(int ncx, int ncy, int m, int ntrain, double* work, RbWork
   RbWork d{};
   d.ns = 3 * ntrain;
   d.n = dual ? d.ns : (int)nI;
-  // a patch has few tiles: the snapshots are summed in parts, which the eigen
-  // kernel adds as it fills LDS (in memory it works on the sum in place)
-  d.parts = dual || d.n > RB_LDS_N ? 1 : 3;
+  // a patch has few tiles: where the patches are few too the snapshots are summed
+  // in parts, which the eigen kernel adds as it fills LDS (in memory it works on
+  // the sum in place)
+  d.parts = dual || d.n > RB_LDS_N || d.n <= RB_TINY || Mc >= RB_MANY ? 1 : 3;
   int64_t off = 0;
   auto take = [&](int64_t count) {
     double* p = work ? work + off : nullptr;
@@ -80,9 +84,9 @@ int64_t rb_work_layout(int ncx, int ncy, int m, int ntrain, double* work, RbWork
 template <typename TA>
 __global__ __launch_bounds__(RB_THREADS) void rb_means_kernel(RbBuildArgs b, RbWork d) {
   __shared__ double part[8][33];
-  const int K = blockIdx.y, m = b.m, nI = (m - 1) * (m - 1), Mc = b.ncx * b.ncy;
+  const int K = blockIdx.x, m = b.m, nI = (m - 1) * (m - 1), Mc = b.ncx * b.ncy;
   const int x = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const int v = blockIdx.x * 32 + x, i = v - m * m;
+  const int v = blockIdx.y * 32 + x, i = v - m * m;
   const int64_t lda = (int64_t)b.ncx * m;
   double acc = 0.0;
   if (v < m * m) {
@@ -133,8 +137,8 @@ __device__ __forceinline__ double rb_psi(const RbBuildArgs& b, int K, int c, int
 
 // W[c][i] = (E Psi)_{i c}: one thread per interior node i, all columns c.
 __global__ __launch_bounds__(RB_THREADS) void rb_energy_kernel(RbBuildArgs b, RbWork d) {
-  const int K = blockIdx.y, m = b.m, n = m - 1, nI = n * n;
-  const int i = blockIdx.x * RB_THREADS + threadIdx.x;
+  const int K = blockIdx.x, m = b.m, n = m - 1, nI = n * n;
+  const int i = blockIdx.y * RB_THREADS + threadIdx.x;
   if (i >= nI) return;
   const int ix = i % n, iy = i / n, px = ix + 1, py = iy + 1;
   const Stencil9 st = rb_stencil(d.abar + (int64_t)K * m * m, m, ix, iy);
@@ -160,9 +164,9 @@ __global__ __launch_bounds__(RB_THREADS) void rb_energy_kernel(RbBuildArgs b, Rb
 constexpr int RBG_T = 64, RBG_K = 32;
 template <bool DUAL>
 __global__ __launch_bounds__(RB_THREADS) void rb_gram_kernel(RbBuildArgs b, RbWork d) {
-  const int K = blockIdx.y, m = b.m, nI = (m - 1) * (m - 1), ns = d.ns, n = d.n;
+  const int K = blockIdx.x, m = b.m, nI = (m - 1) * (m - 1), ns = d.ns, n = d.n;
   const int nt = (n + RBG_T - 1) / RBG_T;
-  int t = blockIdx.x, tc = 0;
+  int t = blockIdx.y, tc = 0;
   while (t >= nt - tc) {  // upper-triangle tile index -> (tc, td), tc <= td
     t -= nt - tc;
     ++tc;
@@ -217,6 +221,22 @@ __global__ __launch_bounds__(RB_THREADS) void rb_gram_kernel(RbBuildArgs b, RbWo
         C[c * ld + r] = acc[u][v];
       }
     }
+}
+
+// H of patches with at most RB_TINY unknowns, where a tile would be nearly empty:
+// an entry per wavefront, its lanes along the snapshots (1024 patches of one
+// unknown 17 us in tiles).
+__global__ __launch_bounds__(RB_THREADS) void rb_gram_tiny_kernel(RbBuildArgs b, RbWork d) {
+  const int K = blockIdx.x, n = d.n, lane = threadIdx.x & 63;
+  double* C = d.C + (int64_t)K * d.parts * n * n;
+  for (int e = threadIdx.x >> 6; e < n * n; e += RB_THREADS / 64) {
+    const int i = e / n, j = e - i * n;
+    if (j < i) continue;
+    double v = 0.0;
+    for (int c = lane; c < d.ns; c += 64) v += rb_psi(b, K, c, i, n) * rb_psi(b, K, c, j, n);
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) C[i * n + j] = C[j * n + i] = v;
+  }
 }
 
 // sum over the 16 lanes of a DPP row, the same bits in all of them
@@ -666,12 +686,12 @@ __global__ __launch_bounds__(RB_EIGEN) void rb_eigen_kernel(RbBuildArgs b, RbWor
 // Element table G of patch K from its modes Zk [nI][rmax] and means pbar
 // [3][nI] (the P coefficients: rb.hip), one coefficient per thread.
 __global__ __launch_bounds__(RB_THREADS) void rb_table_kernel(RbBuildArgs b) {
-  const int K = blockIdx.y;
+  const int K = blockIdx.x;
   const int m = b.m, n = m - 1, nI = n * n, rmax = b.rmax;
   const double* Zk = b.Z + (int64_t)K * nI * rmax;
   const double* pbar = b.phibar + (int64_t)K * 3 * nI;
   const int PP = b.PP, KD = b.KD, NA = rb_na(rmax);
-  for (int ep = blockIdx.x * RB_THREADS + threadIdx.x; ep < KD * PP; ep += gridDim.x * RB_THREADS) {
+  for (int ep = blockIdx.y * RB_THREADS + threadIdx.x; ep < KD * PP; ep += gridDim.y * RB_THREADS) {
     const int e = ep / PP, pidx = ep % PP;
     double val = 0.0;
     if (e < m * m && pidx < rb_p(rmax)) {
@@ -746,7 +766,7 @@ hipError_t launch_rb_build(const RbBuildArgs& b, hipStream_t st) {
   RbWork d;
   rb_work_layout(b.ncx, b.ncy, m, b.ntrain, b.work, &d);
   if (d.n > RB_NMAX) return hipErrorInvalidValue;
-  const dim3 means((m * m + 3 * nI + 31) / 32, Mc);
+  const dim3 means(Mc, (m * m + 3 * nI + 31) / 32);
   if (b.a_dtype == STOMSFEM_F32)
     hipLaunchKernelGGL(rb_means_kernel<float>, means, dim3(RB_THREADS), 0, st, b, d);
   else
@@ -754,10 +774,12 @@ hipError_t launch_rb_build(const RbBuildArgs& b, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nt = (d.n + RBG_T - 1) / RBG_T;
-  const dim3 tiles(nt * (nt + 1) / 2, Mc, d.parts);
+  const dim3 tiles(Mc, nt * (nt + 1) / 2, d.parts);
   if (dual) {
-    hipLaunchKernelGGL(rb_energy_kernel, dim3((nI + RB_THREADS - 1) / RB_THREADS, Mc), dim3(RB_THREADS), 0, st, b, d);
+    hipLaunchKernelGGL(rb_energy_kernel, dim3(Mc, (nI + RB_THREADS - 1) / RB_THREADS), dim3(RB_THREADS), 0, st, b, d);
     hipLaunchKernelGGL(rb_gram_kernel<true>, tiles, dim3(RB_THREADS), 0, st, b, d);
+  } else if (d.n <= RB_TINY) {
+    hipLaunchKernelGGL(rb_gram_tiny_kernel, dim3(Mc), dim3(RB_THREADS), 0, st, b, d);
   } else {
     hipLaunchKernelGGL(rb_gram_kernel<false>, tiles, dim3(RB_THREADS), 0, st, b, d);
   }
@@ -765,8 +787,10 @@ hipError_t launch_rb_build(const RbBuildArgs& b, hipStream_t st) {
   if (e != hipSuccess) return e;
   e = dual ? launch_eigen_any<true>(b, d, st) : launch_eigen_any<false>(b, d, st);
   if (e != hipSuccess) return e;
-  const int cells = b.KD * b.PP;
-  hipLaunchKernelGGL(rb_table_kernel, dim3((cells + RB_THREADS - 1) / RB_THREADS, Mc), dim3(RB_THREADS), 0, st, b);
+  // a coefficient per thread, several where the patches are many: workgroups of
+  // one coefficient take longer to launch than to run (1024 patches at m = 2: 77 us)
+  const int most = (b.KD * b.PP + RB_THREADS - 1) / RB_THREADS, blocks = RB_TABLE_BLOCKS / Mc;
+  hipLaunchKernelGGL(rb_table_kernel, dim3(Mc, blocks < 1 ? 1 : blocks > most ? most : blocks), dim3(RB_THREADS), 0, st, b);
   return hipGetLastError();
 }
 
