@@ -58,18 +58,34 @@ def survey_flops_per_pair(m: int) -> float:
     return nI * (b * b + 2 * b) + 12 * nI * b + 32 * m * m + 250 * m
 
 
+def kernel_source_sha1(name: str) -> str:
+    """sha1 of a kernel's source file and of the headers beside it that it
+    includes, directly or not, in the order in which they are first met."""
+    import hashlib
+    import re
+
+    csrc = os.path.join(ROOT, "paper_1607_00693_amd", "csrc")
+    digest, todo, seen = hashlib.sha1(), [name], {name}
+    while todo:
+        text = open(os.path.join(csrc, todo.pop(0)), "rb").read()
+        digest.update(text)
+        for inc in re.findall(rb'^#include "([^"]+)"', text, re.M):
+            inc = inc.decode()
+            if inc not in seen and os.path.exists(os.path.join(csrc, inc)):
+                seen.add(inc)
+                todo.append(inc)
+    return digest.hexdigest()
+
+
 def profiled_traffic_per_pair():
     """Calibrated HBM bytes per pair of the m = 32 upscaling kernel from the
-    committed counter summary, or None when the kernel source has changed
-    since the counters were taken."""
-    import hashlib
-
+    committed counter summary, or None when the kernel's source or a header of
+    it has changed since the counters were taken."""
     prof = os.path.join(ROOT, "profiles", "upscale_mesh32_hbm_traffic.md")
-    src = os.path.join(ROOT, "paper_1607_00693_amd", "csrc", "upscale_rows.hip")
     try:
         vals = dict(line.split(": ", 1) for line in open(prof).read().splitlines() if ": " in line
                     and line.split(": ", 1)[0] in ("traffic_bytes_per_pair", "kernel_source_sha1"))
-        if hashlib.sha1(open(src, "rb").read()).hexdigest() != vals["kernel_source_sha1"].strip():
+        if kernel_source_sha1("upscale_rows.hip") != vals["kernel_source_sha1"].strip():
             return None
         return float(vals["traffic_bytes_per_pair"])
     except (OSError, KeyError, ValueError):
