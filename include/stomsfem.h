@@ -259,9 +259,9 @@ int stomsfem_coarse_solve_noalloc(int32_t ncx, int32_t ncy, int64_t nsamples, co
  * hold [nsamples][ncy*ncx][16].  S is not symmetric when oversample > 0;
  * oversample = 0 gives the unpacked stiffness of stomsfem_upscale.  The
  * oversampling ratio is M/m (2 for oversample = m/2).  Requires
- * 2 <= M <= 64 and M <= ncx*m, ncy*m (EINVAL otherwise); patches of 4 to 32
- * cells take the kernel with four pairs per wavefront, 33 to 64 cells one
- * pair per wavefront.  Per-pair status
+ * 2 <= M <= 64 and M <= ncx*m, ncy*m (EINVAL otherwise); patches of 2 and 3
+ * cells take the kernel with one pair per lane, 4 to 32 cells four pairs per
+ * wavefront, 33 to 64 cells one pair per wavefront.  Per-pair status
  * ENOTSPD if a pivot is not positive or the corner values of the patch
  * solutions are singular (S undefined).  Asynchronous.
  *

@@ -248,7 +248,7 @@ std::atomic<uint64_t> g_refine_pairs{0}, g_refine_recomputed{0}, g_interp_pairs{
 // coefficient dtype), chosen by stomsfem_autotune (defaults otherwise).
 struct LaunchCfg {
   int lane_block = 64;   // workgroup size of the per-lane kernel (m <= 8)
-  int tiled_waves = 1;   // wavefronts per workgroup of the row-distributed kernel (m = 16, 32)
+  int rows_waves = 1;    // wavefronts per workgroup of the row-distributed kernel (m = 16, 32)
   int precision = STOMSFEM_PREC_F64;
   double ms_default = 0.0, ms_best = 0.0;
   int tuned = 0;
@@ -266,7 +266,7 @@ LaunchCfg tuned_cfg(int m, int a_dtype) {
 
 hipError_t launch_upscale_cfg(const UpArgs& args, int a_dtype, hipStream_t st, const LaunchCfg& c) {
   if (args.m <= 8) return launch_upscale_small(args, a_dtype, st, c.lane_block);
-  if (rows_supports(args.m)) return launch_upscale_rows(args, a_dtype, st, c.tiled_waves);
+  if (rows_supports(args.m)) return launch_upscale_rows(args, a_dtype, st, c.rows_waves);
   return launch_upscale_ref(args, a_dtype, st);
 }
 
@@ -2860,7 +2860,7 @@ int stomsfem_autotune(const stomsfem_batch* batch, int32_t reps, stomsfem_tuning
     out->m = b.m;
     out->a_dtype = b.a_dtype;
     out->lane_block = best.lane_block;
-    out->tiled_waves = best.tiled_waves;
+    out->tiled_waves = best.rows_waves;
     out->precision = best.precision;
     out->ms_default = default_ms;
     out->ms_best = best_ms;

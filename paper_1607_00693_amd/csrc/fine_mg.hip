@@ -32,11 +32,12 @@
 //                sample in LDS, 15.6 us (a launch each for 70 sweeps and
 //                transfers took 180); the thirty sweeps of at most 49 nodes by
 //                one wavefront with its stencil in registers
-//   scalars      the sums of the wavefronts' parts, in a fixed order
+//   scalars      the sums of the wavefronts' parts, in a fixed order that does
+//                not depend on the batch
 // Samples that have converged are left alone.  16 samples of 1024 x 1024, 11
-// iterations: 19.3 -> 7.5 ms; per iteration fmg_down 233 us, fmg_up 149,
-// fmg_step 119 (3.8 to 4.5 TB/s counted without overlap; a copy reaches 5.1),
-// the levels below 146.  One sample of 128 x 128: 2.74 -> 0.75 ms.
+// iterations: 19.3 -> 7.5 ms; per iteration fmg_down 234 us, fmg_up 146,
+// fmg_step 122 (3.8 to 4.5 TB/s counted without overlap; a copy reaches 5.1),
+// the levels below 148.  One sample of 128 x 128: 2.74 -> 0.75 ms.
 //
 // Layout per level and sample: nodes (n+1) x (n+1), elements n x n; sample s
 // of a chunk at offset s (n+1)^2 (nodes) or s n^2 (elements).  Boundary nodes

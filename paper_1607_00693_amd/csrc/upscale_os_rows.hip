@@ -18,7 +18,7 @@
 //
 // FP64-issue bound: at M = 24 a pivot costs 40 window instructions on average,
 // 28 for the right-hand sides and about 20 for the pivot and the products.
-// Measured at M = 24, 131 072 pairs: 12.2 -> 3.5 ms (21.9 TFLOP/s) against the
+// Measured at M = 24, 131 072 pairs: 12.2 -> 3.4 ms (22.9 TFLOP/s) against the
 // ten-lane tile layout it replaced, which moved panel columns and right-hand
 // sides through LDS.
 #include "band_rows.h"
